@@ -135,6 +135,10 @@ def _check(status: int, where: str):
         raise NQError(status, where)
 
 
+_current_raw_stream = torch._C._cuda_getCurrentRawStream if hasattr(torch._C, "_cuda_getCurrentRawStream") else (
+    lambda device: torch.cuda.current_stream(device).cuda_stream)
+
+
 def _ptr(t):
     if t is None:
         return None
@@ -146,7 +150,8 @@ def _ptr(t):
 
 def _stream(s):
     if s is None:
-        return torch.cuda.current_stream().cuda_stream
+        # the raw handle: building a torch.cuda.Stream around it costs more than the rest of a call's argument handling
+        return _current_raw_stream(torch.cuda.current_device())
     if isinstance(s, int):
         return s
     return s.cuda_stream
