@@ -151,11 +151,17 @@ bool plan_smallcin(const Geometry &g, const int8_t *d_x, int64_t n_out, SmallCin
 
 // Patch shape of the depthwise / grouped kernel: the window of a patch must fit the registers that stage
 // it (640 pixels of 64 bytes); among the shapes that do, the one that fetches the fewest halo pixels per
-// output, fills its 16-pixel tiles and still leaves enough units for the whole GPU.
-bool plan_grouped(const Geometry &g, int gs, int64_t C, GroupGeom *gg)
+// output, fills its pixel tiles and still leaves enough units for the whole GPU.  gs_out 0: the kernel for 1, 2 or 4
+// channels per group (64-channel tiles, tiles of 16 pixels dealt to four waves); otherwise the kernel for up to 32
+// channels per group (pairs of half tiles, tiles of 32 pixels dealt to two waves per half tile).
+bool plan_grouped(const Geometry &g, int gs, int gs_out, int64_t C, GroupGeom *gg)
 {
     const int64_t images = g.M / ((int64_t)g.Ho * g.Wo);
-    const int CT = (int)ceil_div(C, 64);
+    const int per_half = gs_out ? 32 / (gs > gs_out ? gs : gs_out) : 0;      // whole groups a half tile covers
+    const int64_t CT64 = gs_out ? ceil_div(C, 2 * per_half * gs_out) : ceil_div(C, 64);
+    if (CT64 > 65535) return false;
+    const int CT = (int)CT64;
+    const int TP = gs_out ? 32 : 16, TW = gs_out ? 2 : 4;
     double best = -1.0;
     int bR = 0, bCW = 0;
     const int tuned_units = g_tune[NQ_TUNE_GC_UNITS].load(std::memory_order_relaxed);
@@ -169,10 +175,10 @@ bool plan_grouped(const Geometry &g, int gs, int64_t C, GroupGeom *gg)
             const int IRp = (R - 1) * g.stride + g.KH;
             if ((int64_t)IRp * ICp > 640 || R * CW > 4000) continue;
             const double halo = (double)R * CW * g.stride * g.stride / ((double)IRp * ICp);
-            const double fill = (double)R * CW / (16.0 * (double)ceil_div(R * CW, 16));
+            const double fill = (double)R * CW / ((double)TP * (double)ceil_div(R * CW, TP));
             const double units = (double)images * (double)ceil_div(g.Ho, R) * (double)ceil_div(g.Wo, CW) * CT;
-            const int64_t pt = ceil_div(R * CW, 16);
-            const double balance = (double)pt / (4.0 * (double)ceil_div(pt, 4));   // tiles are dealt to four waves
+            const int64_t pt = ceil_div(R * CW, TP);
+            const double balance = (double)pt / (TW * (double)ceil_div(pt, TW));   // tiles are dealt to TW waves
             // how many (unit, channel tile) pairs a launch should at least have: measured best at one per
             // resident block, larger patches beating more of them (NQ_TUNE_GC_UNITS overrides)
             const double target = units_target;
@@ -182,6 +188,8 @@ bool plan_grouped(const Geometry &g, int gs, int64_t C, GroupGeom *gg)
     }
     if (best < 0.0) return false;
     gg->gs = gs;
+    gg->gs_out = gs_out; gg->hin = per_half * gs; gg->hout = per_half * gs_out;
+    gg->images = (int)images;
     gg->taps = g.KH * g.KW;
     gg->CT = CT;
     gg->R = bR; gg->CW = bCW;
@@ -190,15 +198,16 @@ bool plan_grouped(const Geometry &g, int gs, int64_t C, GroupGeom *gg)
     const int64_t units = images * gg->RB * gg->CB;
     if (units > 0x3fffffffLL) return false;
     gg->units = (int)units;
-    gg->ptiles = (int)ceil_div(bR * bCW, 16);
+    gg->ptiles = (int)ceil_div(bR * bCW, TP);
     gg->np = (int)ceil_div((int64_t)gg->IRp * gg->ICp * 4, 256);
     gg->cw_magic = (1 << 20) / bCW + 1;
     gg->icp_magic = (1 << 20) / gg->ICp + 1;
     gg->zero_off = gg->IRp * gg->ICp * 80;
     // the decoded weights (8 KiB) and the fragment table (up to 28 KiB) pass through the same memory first
-    const int setup_bytes = 8192 + (gg->taps <= 12 ? 3 : 7) * 4096;
+    // (the decoded weights alone with gs_out: 64 rows of K bytes, rounded up to 64, and 16)
+    const int setup_bytes = gs_out ? 64 * ((int)ceil_div(gg->taps * gs, 64) * 64 + 16) : 8192 + (gg->taps <= 12 ? 3 : 7) * 4096;
     gg->lds_bytes = gg->zero_off + 64 < setup_bytes ? setup_bytes : gg->zero_off + 64;
-    gg->x_bytes = images * g.H * g.W * C;
+    gg->x_bytes = images * g.H * g.W * g.Cin;
     // two resident blocks per compute unit, never more blocks than there are units
     int64_t gx = ceil_div(512, CT);
     if (gx > units) gx = units;
@@ -414,11 +423,24 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         p.conv_big = 0;
         p.cin_shift = 0;
         p.kw_magic = 0;
+        const int general = p.general;
         p.general = 1;
         // four consecutive k are one aligned dword of the input when the group width, the channel count and the
         // pointer are multiples of four
         const int quads = gs % 4 == 0 && g.Cin % 4 == 0 && (reinterpret_cast<uintptr_t>(d_x) & 3u) == 0;
         if (ceil_div(g.M, 32) > 0x7fffffffLL || ceil_div(w->N, 64) > 65535) return NQ_ERR_SHAPE;
+        // Groups of up to 32 channels, whole dwords of input channels, up to nine taps (what a wave holds in registers):
+        // on the matrix cores (32 x 56 x 56 x 256, 32 groups of 8: 24 us against 218 us).  Other widths, filters and
+        // alignments stay with the direct kernel.
+        GroupGeom mg;
+        if (quads && gs <= 32 && gs_out <= 32 && g.KH * g.KW <= 9 && plan_grouped(g, gs, gs_out, w->N, &mg)) {
+            p.general = general;
+            p.kw_magic = 65536 / g.KW + 1;
+            if (!commit()) return NQ_ERR_HIP;
+            g_last_family = 10; g_last_variant = 2;
+            NQ_DISPATCH_HL(h, l, launch_nested_conv_grouped_mid, full, p, mg, s, ev0, ev1);
+            return launch_status();
+        }
         if (!commit()) return NQ_ERR_HIP;
         g_last_family = 10; g_last_variant = quads;
         NQ_DISPATCH_HL(h, l, launch_nested_conv_grouped_any, full, p, gs, gs_out, quads, s, ev0, ev1);
@@ -426,7 +448,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     }
     if (gs > 0) {
         GroupGeom gg;
-        if (!plan_grouped(g, gs, w->N, &gg)) return NQ_ERR_UNSUPPORTED;
+        if (!plan_grouped(g, gs, 0, w->N, &gg)) return NQ_ERR_UNSUPPORTED;
         p.conv_big = 0;
         p.cin_shift = 0;
         p.kw_magic = 65536 / g.KW + 1;      // tap / KW == (tap * kw_magic) >> 16 for the few taps of a filter

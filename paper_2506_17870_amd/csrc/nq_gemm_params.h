@@ -81,14 +81,17 @@ struct SmallCinGeom {
 // Geometry of the depthwise / grouped convolution kernel (work unit = patch of R x CW output pixels of
 // one image).
 struct GroupGeom {
-    int gs;           // channels per group (1, 2 or 4), inputs and outputs alike
-    int taps;         // KH * KW (<= 28)
-    int CT;           // 64-channel tiles = ceil(C / 64)
+    int gs;           // channels per group (1, 2 or 4), inputs and outputs alike; nq_conv_grouped_mid.h: input channels
+    int gs_out;       // nq_conv_grouped_mid.h only: output channels per group, input and output channels of a half tile
+    int hin, hout;    // (its whole groups); 0 otherwise
+    int images;       // B
+    int taps;         // KH * KW (<= 28; nq_conv_grouped_mid.h: <= 9)
+    int CT;           // channel tiles: ceil(C / 64), or pairs of half tiles
     int R, CW;        // output rows and columns of a patch
     int RB, CB;       // patches per image: ceil(Ho / R) x ceil(Wo / CW)
     int IRp, ICp;     // input rows and columns of a patch: (R-1)*stride + KH, (CW-1)*stride + KW
     int units;        // B * RB * CB
-    int ptiles;       // 16-pixel tiles of a patch = ceil(R * CW / 16)
+    int ptiles;       // tiles of 16 (nq_conv_grouped_mid.h: 32) pixels of a patch
     int np;           // 16-byte pieces a thread stages per window = ceil(IRp * ICp * 4 / 256) (<= 10)
     int cw_magic;     // 2^20 / CW + 1: n / CW == (n * cw_magic) >> 20 for n < 4096
     int icp_magic;    // 2^20 / ICp + 1, likewise for window pixels
@@ -164,6 +167,11 @@ void launch_nested_conv_smallcin(bool full, const GemmParams &p, const SmallCinG
 template <int H, int L>
 void launch_nested_conv_grouped(bool full, const GemmParams &p, const GroupGeom &g, hipStream_t st, void *ev_start,
                                 void *ev_stop);
+
+// Grouped convolution with groups of up to 32 channels (whole dwords of them) on either side, up to nine taps.
+template <int H, int L>
+void launch_nested_conv_grouped_mid(bool full, const GemmParams &p, const GroupGeom &g, hipStream_t st, void *ev_start,
+                                    void *ev_stop);
 
 // Grouped convolution with groups of any width and unequal channel counts (direct, on the vector ALU).
 template <int H, int L>
