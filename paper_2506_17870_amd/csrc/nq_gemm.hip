@@ -330,8 +330,10 @@ void fill_params(bool full, const int8_t *d_x, const Geometry &g, const nq_weigh
     p.part_mul = (float)(1 << l);
     p.relu = epi->relu != 0;
     p.out_int8 = epi->out_int8 != 0;
-    // 16-byte activation loads need every chunk of 16 consecutive k inside one pixel
-    p.fast_a = (g.Cin % 16 == 0) && aligned16(d_x);
+    // 16-byte activation loads need every chunk of 16 consecutive k inside one pixel (1); with 8 channels or an odd
+    // multiple of 8 the generic kernel loads halves of 8 (2), else single bytes (0), which costs two divisions each
+    // (1210 x 376 -> 1060 in single bytes: 64 us for the call; by halves of 8, and with small blocks, 13 us).
+    p.fast_a = (g.Cin % 16 == 0) && aligned16(d_x) ? 1 : ((g.Cin % 8 == 0) && ((uintptr_t)d_x & 7u) == 0 ? 2 : 0);
     p.low_signed = w->cfg.low_format == NQ_LOW_SIGNED_L1;
     // the vector epilogue of int8 outputs moves 16 channels at a time; fp32 outputs with a residual
     // (a calibration pass) and the accumulator dump take the element-wise one as well

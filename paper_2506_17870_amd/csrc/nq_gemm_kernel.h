@@ -84,11 +84,28 @@ __global__ void __launch_bounds__(256) k_nested_gemm(const GemmParams p)
         for (int i = 0; i < RPT; ++i) {
             uint4 v = make_uint4(0, 0, 0, 0);
             if (a_ok[i] && k16 < p.K) {
-                if (p.fast_a) {
+                if (p.fast_a == 1) {
                     const int ih = a_ih0[i] + a_kh, iw = a_iw0[i] + a_kw;
                     if ((unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W)
                         v = *reinterpret_cast<const uint4 *>(p.x + a_base[i] +
                                                              ((int64_t)ih * p.W + iw) * p.Cin + a_ci);
+                } else if (p.fast_a == 2) {
+                    // eight bytes are inside one pixel: the chunk's halves may lie in two taps
+                    int kh = a_kh, kw = a_kw, ci = a_ci;
+                    uint2 q[2];
+#pragma unroll
+                    for (int e = 0; e < 2; ++e) {
+                        const int ih = a_ih0[i] + kh, iw = a_iw0[i] + kw;
+                        q[e] = make_uint2(0, 0);
+                        if (k16 + 8 * e < p.K && (unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W)
+                            q[e] = *reinterpret_cast<const uint2 *>(p.x + a_base[i] + ((int64_t)ih * p.W + iw) * p.Cin + ci);
+                        ci += 8;
+                        if (ci >= p.Cin) {
+                            ci -= p.Cin;
+                            if (++kw == p.KW) { kw = 0; ++kh; }
+                        }
+                    }
+                    v = make_uint4(q[0].x, q[0].y, q[1].x, q[1].y);
                 } else {
                     uint32_t w[4] = {0, 0, 0, 0};
                     for (int e = 0; e < 16; ++e) {
