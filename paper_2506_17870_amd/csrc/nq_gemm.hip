@@ -218,12 +218,12 @@ bool plan_grouped(const Geometry &g, int gs, int gs_out, int64_t C, GroupGeom *g
     return true;
 }
 
-// Decides whether the stationary-weights GEMM applies (1x1 filter without padding, K = 64, 128 or 256) and
+// Decides whether the stationary-weights GEMM applies (1x1 filter without padding, K up to 256) and
 // works out its geometry.
 bool plan_stat(const Geometry &g, const int8_t *d_x, int64_t N, int64_t K, StatGeom *sg)
 {
     if (g.KH != 1 || g.KW != 1 || g.pad != 0 || g.Cin != K) return false;
-    if (K != 64 && K != 128 && K != 256) return false;
+    if (K < 16 || K > 256 || K % 16 != 0) return false;       // whole 16-byte pieces
     if (!aligned16(d_x) || N < 1) return false;
     const int64_t howo = (int64_t)g.Ho * g.Wo;
     const int64_t images = g.M / howo;
@@ -234,7 +234,7 @@ bool plan_stat(const Geometry &g, const int8_t *d_x, int64_t N, int64_t K, StatG
     // the divisions by Ho * Wo and by Wo are multiplications by a rounded-up reciprocal: exact while
     // dividend * divisor < 2^32 (dividends: a row index inside an image plus one tile; a pixel index)
     if (strided && ((howo + 256) * howo >= (int64_t(1) << 32) || howo * g.Wo >= (int64_t(1) << 32))) return false;
-    sg->ks = (int)(K / 64);
+    sg->ks = K <= 64 ? 1 : (K <= 128 ? 2 : 4);
     sg->wn = N <= 64 ? 1 : (N <= 128 ? 2 : 4);
     sg->cgroups = (int)ceil_div(N, 64 * sg->wn);
     if (sg->cgroups > 0x3fffff) return false;
@@ -491,7 +491,12 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     }
     // short reductions without a filter window: weights stationary in registers, rows streamed
     StatGeom tg;
-    if ((force == 9 || (force == 0 && g.M > 64)) && plan_stat(g, d_x, w->N, w->K, &tg)) {
+    // (a K other than 64, 128 or 256 pays for its panels' padding: ahead of the generic kernel on many rows, 78400 x 32 ->
+    // 128: 9.6 us against 18.0, 313600 x 16 -> 64: 14.2 against 17.4, and behind it on few rows or few columns, 19600 x 32
+    // -> 256: 8.4 against 7.0, 78400 x 144 -> 64: 14.1 against 9.6)
+    const bool stat_wanted = w->K == 64 || w->K == 128 || w->K == 256 ||
+                             (g.M >= 40000 && (w->N > 64 || (g.M >= 200000 && w->K <= 64)));
+    if ((force == 9 || (force == 0 && g.M > 64 && stat_wanted)) && plan_stat(g, d_x, w->N, w->K, &tg)) {
         if (!commit()) return NQ_ERR_HIP;
         g_last_family = 9; g_last_variant = tg.wn;
         NQ_DISPATCH_HL(h, l, launch_nested_gemm_stat, full, p, tg, s, ev0, ev1);

@@ -1,4 +1,4 @@
-// Nested-integer GEMM for short reductions (K = 64, 128 or 256: the 1x1 convolutions of a CNN with that
+// Nested-integer GEMM for short reductions (K up to 256, a multiple of 16: the 1x1 convolutions of a CNN with that
 // many input channels, at any stride), weights stationary in registers (paper Sec. 3.3: full-bit =
 // w_high * 2^l + w_low recomposed on the fly, Eq. 4; part-bit = w_high with the scale s * 2^l, Eq. 8;
 // 8-bit activations, Sec. 4.2).
@@ -17,7 +17,12 @@
 // (oh * stride, ow * stride) of its image, so only the pixels the layer needs are fetched.  Rows past M are
 // requested out of the descriptor's range, which reads as zero.
 //
-// Panel layout: BM rows of K bytes, not padded (a wave-wide LDS-direct load writes 1024 contiguous bytes).
+// K is rounded up to KS K steps of 64 (1, 2 or 4): the panel's pieces past K are requested out of range and are zero,
+// and K steps past the page's last one repeat its weights, which then meet zeros.  A K of 32 or 96 or 144 (the 1x1 layers
+// of a MobileNet) went to the generic kernel before, which starts a block per tile:
+// 78400 x 32 -> 128 took 18.0 us there and takes 9.6 us here.
+//
+// Panel layout: BM rows of 64 * KS bytes, not padded (a wave-wide LDS-direct load writes 1024 contiguous bytes).
 // The 16-byte pieces of row r are stored at position c ^ f(r), f chosen so that the sixteen rows a 16-byte
 // LDS read serves together fall into sixteen different bank groups: f(r) = r & 15 for rows of 256 bytes or
 // more, (r >> 1) & 7 for 128 bytes, (r >> 2) & 3 for 64 bytes.
@@ -39,9 +44,11 @@ typedef unsigned s_u4v __attribute__((__vector_size__(4 * sizeof(unsigned))));  
 
 constexpr int ST_OOR = 0x7fff0000;            // beyond every descriptor range (the host keeps inputs smaller)
 
-// KS: K steps of 64 (1, 2 or 4: exact, so that the decoded weights are a register array and the K loop is
+// KS: K steps of 64 (1, 2 or 4: a constant, so that the decoded weights are a register array and the K loop is
 // straight-line code).  WN: waves along N (4: 256 columns per block; 2: 128; 1: 64).
-template <int H, int L, int FULL, int EPI, int KS, int WN>
+// EXACT: K = 64 * KS; the offsets of a lane's rows and weight tiles are then constants (with the general form in its place
+// a 100352 x 256 -> 256 layer took 24.7 us against 20.5 us).
+template <int H, int L, int FULL, int EPI, int KS, int WN, bool EXACT>
 __global__ void __launch_bounds__(256, EPI == EPI_ANY ? 1 : 2) k_nested_gemm_stat(const GemmParams p, const StatGeom g)
 {
     constexpr int S = 8 - H;
@@ -97,7 +104,7 @@ __global__ void __launch_bounds__(256, EPI == EPI_ANY ? 1 : 2) k_nested_gemm_sta
     }
     int pan_lane[LW];
 #pragma unroll
-    for (int j = 0; j < LW; ++j) pan_lane[j] = ld_row[j] * ROWB + ld_c16[j];
+    for (int j = 0; j < LW; ++j) pan_lane[j] = ld_row[j] * (EXACT ? ROWB : p.K) + ld_c16[j];
     // output / residual offsets: lane part of tile (t, i) = out0 + i * n32 + t * 32 (see NQ_ST_OUT_OFF below)
     const int brow0 = wm * 32 * TM + (lane & 31), ch0 = nb0 * 32 + 16 * (lane >> 5);
     const int out0 = brow0 * (int)p.N + ch0, n32 = 32 * (int)p.N;
@@ -124,11 +131,11 @@ __global__ void __launch_bounds__(256, EPI == EPI_ANY ? 1 : 2) k_nested_gemm_sta
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
 #pragma unroll
-                for (int i = 0; i < H; ++i) W8[t][s][i] = ph[(unsigned)(s * (H * 64) + wslot * H + i)];
+                for (int i = 0; i < H; ++i) W8[t][s][i] = ph[(unsigned)((EXACT ? s : min(s, p.KB - 1)) * (H * 64) + wslot * H + i)];
                 if constexpr (FULL != 0) {
 #pragma unroll
                     for (int i = 0; i < LP::DW; ++i)
-                        W8[t][s][H + i] = pl[(unsigned)(s * (LP::DW * 64) + wslot * LP::DW + i)];
+                        W8[t][s][H + i] = pl[(unsigned)((EXACT ? s : min(s, p.KB - 1)) * (LP::DW * 64) + wslot * LP::DW + i)];
                 }
             }
         }
@@ -163,12 +170,12 @@ __global__ void __launch_bounds__(256, EPI == EPI_ANY ? 1 : 2) k_nested_gemm_sta
             b0 = (int)(m0 / g.howo);
             rem0 = (int)(m0 - (int64_t)b0 * g.howo);
         } else if (real) {
-            pbase = (int)(m0 * ROWB);
+            pbase = (int)(m0 * (EXACT ? ROWB : p.K));
         }
 #pragma unroll
         for (int j = 0; j < LW; ++j) {
             const int k = wave * LW + j;
-            const bool in = k < NWL && ld_row[j] < rl;
+            const bool in = k < NWL && ld_row[j] < rl && (EXACT || ld_c16[j] < p.K);     // pieces past K read as zero
             int off;
             if (g.strided) {
                 const unsigned n = (unsigned)(rem0 + ld_row[j]);
@@ -487,9 +494,9 @@ void launch_nested_gemm_stat(bool full, const GemmParams &p, const StatGeom &g, 
 {
     const dim3 grid((unsigned)(((g.nslots + 7) / 8) * 8 * g.cgroups)), block(256);
     const int mode = epi_mode(p);
-#define NQ_ST_LAUNCH(FULLV, EPIV, KSV, WNV)                                                     \
+#define NQ_ST_LAUNCH(FULLV, EPIV, KSV, WNV, EXACTV)                                             \
     do {                                                                                        \
-        auto k = k_nested_gemm_stat<H, L, FULLV, EPIV, KSV, WNV>;                               \
+        auto k = k_nested_gemm_stat<H, L, FULLV, EPIV, KSV, WNV, EXACTV>;                       \
         const size_t lds = st_lds_bytes(KSV, WNV);                                              \
         static bool granted = false;                                                            \
         if (!granted) {                                                                         \
@@ -499,17 +506,20 @@ void launch_nested_gemm_stat(bool full, const GemmParams &p, const StatGeom &g, 
         }                                                                                       \
         launch_timed(k, grid, block, lds, st, ev_start, ev_stop, p, g);                         \
     } while (0)
-#define NQ_ST_WN(FULLV, EPIV, KSV)                               \
-    do {                                                         \
-        if (g.wn == 4) NQ_ST_LAUNCH(FULLV, EPIV, KSV, 4);        \
-        else if (g.wn == 2) NQ_ST_LAUNCH(FULLV, EPIV, KSV, 2);   \
-        else NQ_ST_LAUNCH(FULLV, EPIV, KSV, 1);                  \
+#define NQ_ST_WN(FULLV, EPIV, KSV, EXACTV)                               \
+    do {                                                                 \
+        if (g.wn == 4) NQ_ST_LAUNCH(FULLV, EPIV, KSV, 4, EXACTV);        \
+        else if (g.wn == 2) NQ_ST_LAUNCH(FULLV, EPIV, KSV, 2, EXACTV);   \
+        else NQ_ST_LAUNCH(FULLV, EPIV, KSV, 1, EXACTV);                  \
     } while (0)
-#define NQ_ST_KS(FULLV, EPIV)                                    \
-    do {                                                         \
-        if (g.ks == 4) NQ_ST_WN(FULLV, EPIV, 4);                 \
-        else if (g.ks == 2) NQ_ST_WN(FULLV, EPIV, 2);            \
-        else NQ_ST_WN(FULLV, EPIV, 1);                           \
+#define NQ_ST_KS(FULLV, EPIV)                                            \
+    do {                                                                 \
+        if (p.K == 256) NQ_ST_WN(FULLV, EPIV, 4, true);                  \
+        else if (p.K == 128) NQ_ST_WN(FULLV, EPIV, 2, true);             \
+        else if (p.K == 64) NQ_ST_WN(FULLV, EPIV, 1, true);              \
+        else if (g.ks == 4) NQ_ST_WN(FULLV, EPIV, 4, false);             \
+        else if (g.ks == 2) NQ_ST_WN(FULLV, EPIV, 2, false);             \
+        else NQ_ST_WN(FULLV, EPIV, 1, false);                            \
     } while (0)
 #define NQ_ST_MODES(FULLV)                                       \
     do {                                                         \
