@@ -347,7 +347,7 @@ nq_status nq_gconv_part(const int8_t *d_x, const nq_conv_shape *shape, int group
  * does not apply to a shape is ignored for that call.  Meant to be set while no other thread is inside
  * the library (the parity tests run every case once per kernel that can take it).
  *   NQ_TUNE_KERNEL:   1 generic, 2 windowed, 3 register-stationary, 4 large GEMM, 5 few input channels,
- *                     6 few rows, 9 stationary-weights GEMM (short reductions)
+ *                     6 few rows, 9 stationary-weights GEMM (short reductions), 11 small outputs (32 x 32 blocks)
  *   NQ_TUNE_BIG_TM:   2..5, rows per block of the large-GEMM kernel = 32 * value; 6 = 128 rows with one block
  *                     per compute unit (the whole register file: deeper weight pipeline); 7 = blocks of 128 rows
  *                     x 128 columns (the library's choice for up to 128 output channels)

@@ -3,7 +3,7 @@
     python -m paper_2506_17870_amd.build [--force]
 
 Objects go to _build/ next to this file, the library to paper_2506_17870_amd/libnq.so.
-Four translation units per nesting (h, l) hold the GEMM/convolution kernels, so the
+Five translation units per nesting (h, l) hold the GEMM/convolution kernels, so the
 units compile in parallel; the GEMM over the paper's word pages is one unit for all nestings.
 """
 from __future__ import annotations
@@ -33,6 +33,8 @@ def _units():
         for part in (1, 0, 2, 3):
             units.append((os.path.join(CSRC, "nq_gemm_inst.hip"), os.path.join(OBJ, f"nq_gemm_inst_{h}{l}_{part}.o"),
                           [f"-DNQ_INST_H={h}", f"-DNQ_INST_L={l}", f"-DNQ_INST_PART={part}"]))
+        units.append((os.path.join(CSRC, "nq_gemm_slab.hip"), os.path.join(OBJ, f"nq_gemm_slab_{h}{l}.o"),
+                      [f"-DNQ_INST_H={h}", f"-DNQ_INST_L={l}"]))
     return units
 
 

@@ -11,6 +11,12 @@
 
 using namespace nq;
 
+namespace nq {
+// Outputs too small for the large kernel's tiles (nq_gemm_slab.h, instantiated per nesting by nq_gemm_slab.hip).
+template <int H, int L>
+void launch_nested_gemm_slab(bool full, const GemmParams &p, int x_bytes, hipStream_t st, void *ev_start, void *ev_stop);
+}  // namespace nq
+
 namespace {
 
 struct Geometry {
@@ -269,6 +275,16 @@ bool plan_stat(const Geometry &g, const int8_t *d_x, int64_t N, int64_t K, StatG
     return true;
 }
 
+// Whether the small-output kernel (nq_gemm_slab.h) can take the problem: vector epilogue, 32-bit offsets, dword-aligned
+// rows; a filter needs the 32 bytes a lane reads of a K step inside one tap.
+bool slab_ok(const Geometry &g, const int8_t *d_x, int64_t K, int64_t x_bytes, bool general)
+{
+    if (general || ((uintptr_t)d_x & 3u) != 0 || g.Cin % 4 != 0) return false;
+    if (x_bytes >= 0x7fff0000LL - (1 << 18) || g.M > 65535 * 32) return false;
+    const bool one_tap = g.Cin == K && g.pad == 0;
+    return one_tap || (g.Cin % 32 == 0 && g.KH * g.KW * g.KW < 65536);
+}
+
 int pick_tile(int64_t M, int64_t N)
 {
     if (N <= 64) return 0;
@@ -460,7 +476,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         return launch_status();
     }
     // NQ_TUNE_KERNEL (test and tuning aid): 1 generic, 2 windowed, 3 register-stationary, 4 large GEMM,
-    // 5 few input channels, 6 few rows, 9 stationary-weights GEMM;
+    // 5 few input channels, 6 few rows, 9 stationary-weights GEMM, 11 small outputs;
     // a kernel that does not apply to the shape is never forced, the choice falls through.
     const int force = g_tune[NQ_TUNE_KERNEL].load(std::memory_order_relaxed);
     const bool plain_gemm = g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0 && w->K % 256 == 0 && aligned16(d_x);
@@ -489,6 +505,27 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         if (conv_gemm && w->N <= 64 && g.stride == 1 && g.KH * g.KW > 1 && plan_window(g, d_x, &wg0, &lds0))
             big_wanted = false;
     }
+    // Outputs too small to fill the chip with large tiles: 32 x 32 blocks that split K over their waves.  Up to one block
+    // per compute unit they are ahead of every other kernel (197 x 3072 -> 768: 7.7 us against 16.7 us for the large one;
+    // 196 x 2304 -> 256 3x3: 7.2 against 14.8; 800 x 256 -> 256: 4.1 against 9.4 for the stationary one; 49 x 4608 -> 512
+    // 3x3: 9.4 against 61.3 for the windowed one).  Up to two per unit they are ahead where the reduction is long (416
+    // blocks, K = 4096: 15.7 against 20.6) or short (400 blocks, K = 256: 4.8 against 9.5), and behind in between (384
+    // blocks, K = 768: 9.0 against 8.3).  Up to 32 rows, and up to 64 with more blocks than units, the kernel for few
+    // rows has the same split and reads the weights once (16 x 1024 -> 4096: 4.1 against 4.8; 64 x 512 -> 512 the other
+    // way round, 4.8 against 4.1).  A single K step leaves three of four waves without work and is not taken.
+    const bool slab_fits = slab_ok(g, d_x, w->K, x_bytes, p.general != 0);
+    const bool skinny_ok = g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0 && g.M <= 64 && w->K % 16 == 0 &&
+                           aligned16(d_x) && ceil_div(w->N, 32) <= 0x7fffffffLL;
+    const int64_t slab_blocks = ceil_div(g.M, 32) * ceil_div(w->N, 32);
+    const bool slab_wanted = (slab_blocks <= 256 || (slab_blocks <= 512 && (w->K <= 512 || w->K >= 2048))) &&
+                             w->K > 64 && !(skinny_ok && w->K >= 256 && (g.M <= 32 || slab_blocks > 256));
+    auto run_slab = [&]() {
+        if (!commit()) return NQ_ERR_HIP;
+        g_last_family = 11; g_last_variant = 0;
+        NQ_DISPATCH_HL(h, l, launch_nested_gemm_slab, full, p, (int)x_bytes, s, ev0, ev1);
+        return launch_status();
+    };
+    if (slab_fits && (force == 11 || (force == 0 && slab_wanted))) return run_slab();
     // short reductions without a filter window: weights stationary in registers, rows streamed
     StatGeom tg;
     // (a K other than 64, 128 or 256 pays for its panels' padding: ahead of the generic kernel on many rows, 78400 x 32 ->
@@ -512,8 +549,6 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         return launch_status();
     }
     // few rows: the packed weights are the traffic; one block per 32 columns, K split over the waves
-    const bool skinny_ok = g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0 && g.M <= 64 && w->K % 16 == 0 &&
-                           aligned16(d_x) && ceil_div(w->N, 32) <= 0x7fffffffLL;
     if (skinny_ok && (force == 6 || (force == 0 && w->K >= 256))) {
         if (!commit()) return NQ_ERR_HIP;
         g_last_family = 6; g_last_variant = 0;
@@ -546,6 +581,10 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         NQ_DISPATCH_HL(h, l, launch_nested_conv_window, full, 0, p, wg, lds, s, ev0, ev1);
         return launch_status();
     }
+    // What is left would go to the generic kernel, whose 128 x 256 tiles walk K one step at a time: small blocks again,
+    // up to the number at which both take as long (K = 1000, N = 1000: 1600 blocks 13.0 us against 23.8, 3200 blocks 23.0
+    // against 24.7; K = 200, N = 2048: 832 blocks 7.4 against 9.9, 1600 blocks 11.2 against 9.9).
+    if (slab_fits && force == 0 && slab_blocks <= (w->K >= 512 ? 2560 : 1024)) return run_slab();
     const int tile = pick_tile(g.M, w->N);
     if (ceil_div(g.M, NQ_TILE_BM[tile]) > 0x7fffffffLL || ceil_div(w->N, NQ_TILE_BN[tile]) > 65535)
         return NQ_ERR_SHAPE;
