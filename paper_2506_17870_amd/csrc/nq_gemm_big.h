@@ -1,7 +1,9 @@
 // Nested-integer GEMM main loop for large problems (paper Sec. 3.3: full-bit = w_high * 2^l +
 // w_low recomposed on the fly, Eq. 4; part-bit = w_high with the scale s * 2^l, Eq. 8).  Also
 // serves convolutions: 1x1 stride 1 is a GEMM over the NHWC pixels as it stands, and with CONV
-// any filter over a power-of-two number of input channels (>= 16) is an implicit GEMM in which
+// any filter over a multiple of 16 input channels, and any GEMM whose K is a multiple of 16 but not of 256 (as a
+// filter of one tap: the test that drops taps past K keeps a row's last pieces out of the next row), is an implicit
+// GEMM in which
 // every 16-byte piece of an activation row is fetched from the input pixel its filter tap points
 // at (or from out of range, which reads as zero, for the padding and for the tail of K).
 //
@@ -203,7 +205,7 @@ __global__ void __launch_bounds__(256, ((TMX <= 4 || TMX == 7) && EPI != EPI_ANY
             a_goff[par] = (wave * (4 * APT) + (lane >> 4)) * p.K + 16 * piece[par];
     }
     // CONV: where the lane's four pieces of iteration `it` come from: the k index of a piece -> filter tap
-    // and channel (Cin is a power of two).  Worked out once per iteration, used by all its requests.
+    // and channel.  Worked out once per iteration, used by all its requests.
     // (24-bit multiplications: full rate on the vector ALU, where a 32-bit one takes four issue slots; a filter has
     // at most 15 x 16 taps and the image at most 8192 columns)
     int tap_off[4], tap_hw[4];
@@ -211,9 +213,9 @@ __global__ void __launch_bounds__(256, ((TMX <= 4 || TMX == 7) && EPI != EPI_ANY
 #pragma unroll
         for (int par = 0; par < 4; ++par) {
             const int kk = it * (GB_KI * 64) + 16 * piece[par];
-            const int tap = kk >> p.cin_shift, ci = kk & (p.Cin - 1);
+            const int tap = (int)__umulhi((unsigned)kk, p.cin_magic), ci = kk - __mul24(tap, p.Cin);
             const int kh = __mul24(tap, p.kw_magic) >> 16, kw = tap - __mul24(kh, p.KW);
-            tap_off[par] = ((__mul24(kh, p.W) + kw) << p.cin_shift) + ci;
+            tap_off[par] = __mul24(__mul24(kh, p.W) + kw, p.Cin) + ci;
             // the tap's bits in a pixel's table entry; a piece past the end of K gets bit 15, which no pixel has
             tap_hw[par] = kk < p.K ? (int)((1u << kh) | (0x10000u << kw)) : 0x8000;
         }

@@ -23,8 +23,10 @@ struct GemmParams {
     int relu, out_int8, fast_a;
     int low_signed;   // lower-bit page holds signed fields of l + 1 bits (compensated format)
     int general;   // 1: the element-wise epilogue is needed (set by the host from the arguments)
-    // implicit GEMM of the large-GEMM kernel: Cin = 2^cin_shift, tap / KW = (tap * kw_magic) >> 16
-    int conv_big, cin_shift, kw_magic;
+    // implicit GEMM of the large-GEMM kernel: k / Cin = umulhi(k, cin_magic), tap / KW = (tap * kw_magic) >> 16
+    int conv_big;
+    unsigned cin_magic;
+    int kw_magic;
 };
 
 // Geometry of the LDS-resident input window of the windowed convolution kernel.

@@ -1,0 +1,191 @@
+"""GPU parity, against the CPU oracle, of the kernels and dispatch branches for layers between the large tiles: outputs
+too small to fill the chip (32 x 32 blocks, the reduction split over the waves), short reductions that are no power of
+two, activations in steps of eight channels, groups of up to 32 channels, and the one-launch quantiser + packer.  Integer
+sums in a fixed fp32 epilogue: everything is compared for equality."""
+import numpy as np
+import pytest
+import torch
+
+import nq_testlib as tl
+from nq_testlib import Case, check_outputs, dev, epi_pair, host, run_gconv_both, set_choice
+from oracle import nq_oracle as oracle
+from paper_2506_17870_amd import inputs
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def nq():
+    import paper_2506_17870_amd as nq
+    assert torch.cuda.is_available()
+    return nq
+
+
+def make_case(nq, N, K, n, l, seed, compensated=False):
+    w_int, scale = tl.weights(N, K, inputs.he_sigma(K), n, seed)
+    c = Case(nq, w_int, scale, n, l)
+    if compensated:
+        c.cfg = nq.make_cfg(n, l, nq.NQ_LOW_SIGNED_L1)
+        c.W = nq.NestedWeight.from_int8(dev(w_int), dev(scale), c.cfg)
+        c.ow_part = oracle.decompose(w_int, n, l, "rtn")[0].astype(np.int16)
+        c.ow_full = w_int.astype(np.int16)
+    return c
+
+
+def forced(nq, case, x, shape, choice, family=None):
+    """A GEMM (x [M, K], shape None) or a convolution with one kernel forced: fp32 with bias, int8 with and without a
+    residual where 16-channel stores apply, full-bit and part-bit."""
+    conv = shape is not None
+    if conv:
+        B, H, W, Cin = x.shape
+        KH, KW, stride, pad = shape
+        Ho, Wo = oracle.conv_out_hw(H, W, KH, KW, stride, pad)
+        lead = (B, Ho, Wo)
+        cs = nq.nq_conv_shape(B, H, W, Cin, case.N, KH, KW, stride, pad)
+    else:
+        lead = (x.shape[0],)
+    dx, N = dev(x), case.N
+    bias = inputs.small_floats(N, 0.2, seed=N)
+    res = inputs.uniform_activations(lead + (N,), seed=N + 1)
+    runs = [dict(s_a=0.02, bias=bias)]
+    if N % 16 == 0:
+        runs += [dict(s_a=0.02, out_int8=True, inv_s_out=4.0),
+                 dict(s_a=0.02, bias=bias, residual=res, s_r=0.05, relu=True, out_int8=True, inv_s_out=4.0)]
+    for full in (True, False):
+        w = case.ow_full if full else case.ow_part
+        acc = oracle.conv_acc(x, w.reshape(N, KH, KW, Cin), stride, pad) if conv else oracle.gemm_acc(x, w)
+        for kw in runs:
+            epi, keep, okw = epi_pair(nq, case, full, lead, dump=False, **kw)
+            i8 = kw.get("out_int8", False)
+            y = torch.full(lead + (N,), 77, dtype=torch.int8 if i8 else torch.float32, device="cuda")
+            set_choice(choice)
+            try:
+                if conv:
+                    (nq.nq_conv_full if full else nq.nq_conv_part)(dx, cs, case.W.desc, epi, y)
+                else:
+                    (nq.nq_gemm_full if full else nq.nq_gemm_part)(dx, x.shape[0], case.W.desc, epi, y)
+            finally:
+                set_choice("")
+            torch.cuda.synchronize()
+            if family is not None:
+                assert nq.nq_profile_last_kernel()[0] == family
+            check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, i8)
+
+
+# ---- small outputs: 32 x 32 blocks ------------------------------------------------------------------------------
+@pytest.mark.parametrize("M,N,K", [(1, 1, 4), (33, 40, 60), (32, 32, 64), (31, 48, 68), (197, 96, 1000), (65, 80, 768),
+                                   (64, 2048, 2052), (300, 16, 4096), (5, 31, 8192)])
+def test_small_outputs_gemm(nq, M, N, K):
+    # rows and columns off the tile, K steps fewer than waves, ends of K inside a lane's 32 bytes, eight and four waves
+    forced(nq, make_case(nq, N, K, 8, 2, seed=M + N + K), inputs.uniform_activations((M, K), seed=K), None, "11", 11)
+
+
+@pytest.mark.parametrize("B,H,W,Cin,N,k,stride,pad", [
+    (1, 7, 7, 512, 64, 3, 1, 1), (2, 5, 6, 32, 48, 3, 1, 1), (1, 9, 8, 96, 33, 3, 2, 1), (1, 8, 8, 64, 32, 5, 1, 2),
+    (3, 6, 5, 128, 64, 1, 2, 0), (1, 5, 5, 36, 32, 1, 2, 0), (1, 4, 4, 64, 32, 1, 1, 1), (1, 3, 3, 32, 16, 3, 1, 0)])
+def test_small_outputs_filters(nq, B, H, W, Cin, N, k, stride, pad):
+    forced(nq, make_case(nq, N, k * k * Cin, 8, 3, seed=Cin + N + k), inputs.uniform_activations((B, H, W, Cin), seed=H),
+           (k, k, stride, pad), "11", 11)
+
+
+@pytest.mark.parametrize("n,l", [(8, l) for l in range(1, 7)] + [(6, l) for l in range(1, 5)])
+@pytest.mark.parametrize("compensated", [False, True])
+def test_small_outputs_every_nesting(nq, n, l, compensated):
+    x = inputs.uniform_activations((70, 1152), seed=l) >> (8 - n)
+    forced(nq, make_case(nq, 48, 1152, n, l, seed=n + l, compensated=compensated), x, None, "11", 11)
+    x = inputs.uniform_activations((1, 6, 6, 64), seed=l) >> (8 - n)
+    forced(nq, make_case(nq, 48, 576, n, l, seed=n * l, compensated=compensated), x, (3, 3, 1, 1), "11", 11)
+
+
+def test_small_outputs_by_the_library(nq):
+    """The dispatch itself takes these to the small-output kernel, and to it alone."""
+    forced(nq, make_case(nq, 768, 3072, 8, 3, seed=1), inputs.uniform_activations((197, 3072), seed=1), None, "", 11)
+    forced(nq, make_case(nq, 256, 2304, 8, 2, seed=2), inputs.uniform_activations((1, 14, 14, 256), seed=2), (3, 3, 1, 1), "", 11)
+
+
+# ---- short reductions in steps of 16, activations in steps of 8 ------------------------------------------------
+@pytest.mark.parametrize("M,N,K", [(100, 64, 16), (333, 96, 32), (333, 144, 48), (4097, 192, 96), (129, 272, 144),
+                                   (700, 64, 192), (257, 40, 240)])
+def test_stationary_weights_any_short_reduction(nq, M, N, K):
+    for n, l, comp in ((8, 2, False), (6, 3, False), (8, 5, True)):
+        x = inputs.uniform_activations((M, K), seed=K) >> (8 - n)
+        forced(nq, make_case(nq, N, K, n, l, seed=M + K + l, compensated=comp), x, None, "9", 9)
+
+
+def test_stationary_weights_strided_short_reduction(nq):
+    x = inputs.uniform_activations((3, 13, 11, 48), seed=3)
+    forced(nq, make_case(nq, 96, 48, 8, 3, seed=3), x, (1, 1, 2, 0), "9", 9)
+
+
+@pytest.mark.parametrize("Cin,k,stride,pad", [(8, 3, 1, 1), (24, 3, 2, 1), (40, 1, 1, 0), (72, 5, 1, 2)])
+def test_activations_in_steps_of_eight(nq, Cin, k, stride, pad):
+    x = inputs.uniform_activations((2, 9, 10, Cin), seed=Cin)
+    forced(nq, make_case(nq, 80, k * k * Cin, 8, 2, seed=Cin), x, (k, k, stride, pad), "1", 1)
+
+
+# ---- the large kernel: channel counts and reductions that are no power of two --------------------------------------
+@pytest.mark.parametrize("choice", ["4", "4/tm2", "4/tm3", "4/tm5", "4/tm6", "4/tm7"])
+def test_large_kernel_any_multiple_of_sixteen(nq, choice):
+    # K one piece past a panel, one piece short of one, shorter than one; rows off the tile
+    for M, N, K in ((300, 320, 272), (130, 272, 1008), (333, 96, 48), (200, 528, 2032)):
+        forced(nq, make_case(nq, N, K, 8, 2, seed=K), inputs.uniform_activations((M, K), seed=M), None, choice, 4)
+    for B, H, W, Cin, N, k, stride, pad in ((2, 9, 8, 48, 144, 3, 1, 1), (1, 13, 11, 80, 272, 5, 2, 2), (3, 12, 9, 208, 96, 1, 2, 0),
+                                            (2, 7, 7, 112, 320, 2, 1, 0)):
+        forced(nq, make_case(nq, N, k * k * Cin, 8, 3, seed=Cin), inputs.uniform_activations((B, H, W, Cin), seed=H),
+               (k, k, stride, pad), choice, 4)
+
+
+# ---- groups of up to 32 channels ------------------------------------------------------------------------------
+@pytest.mark.parametrize("geom", [
+    # B, H, W, Cin, Cout, groups, KH, stride, pad
+    (1, 9, 9, 24, 24, 3, 3, 1, 1),        # 8 per group; a pixel's second piece reaches past its channels
+    (2, 7, 6, 36, 36, 3, 3, 1, 1),        # 12 per group: half tiles of 24 channels, the last one of 12
+    (1, 11, 9, 96, 96, 8, 3, 2, 1),       # 12 per group, two channel tiles, stride 2
+    (1, 56, 33, 256, 256, 32, 3, 1, 1),   # patches of several tiles, ragged in both directions
+    (2, 5, 5, 48, 48, 3, 3, 1, 1),        # 16 per group, the second half tile half empty
+    (1, 8, 8, 96, 96, 3, 1, 1, 0),        # 32 per group, 1x1
+    (1, 6, 7, 64, 16, 4, 2, 1, 0),        # 16 in, 4 out; 2x2
+    (1, 6, 7, 16, 64, 4, 3, 1, 1),        # 4 in, 16 out
+])
+def test_groups_on_the_matrix_cores(nq, geom):
+    B, H, W, Cin, Cout, groups, KH, stride, pad = geom
+    K = KH * KH * (Cin // groups)
+    Ho, Wo = (H + 2 * pad - KH) // stride + 1, (W + 2 * pad - KH) // stride + 1
+    x = inputs.uniform_activations((B, H, W, Cin), seed=Cin + H)
+    bias = inputs.small_floats(Cout, 0.1, seed=3)
+    res = inputs.uniform_activations((B, Ho, Wo, Cout), seed=Cout)
+    for n, l, comp in ((8, 2, False), (6, 3, True)):
+        case = make_case(nq, Cout, K, n, l, seed=sum(geom) + l, compensated=comp)
+        for full in (True, False):
+            run_gconv_both(nq, case, x, (KH, KH, stride, pad), groups, full, s_a=0.02, bias=bias)
+            run_gconv_both(nq, case, x, (KH, KH, stride, pad), groups, full, s_a=0.02, bias=bias, out_int8=True, inv_s_out=5.0)
+            run_gconv_both(nq, case, x, (KH, KH, stride, pad), groups, full, s_a=0.02, bias=bias, residual=res, s_r=0.04,
+                           relu=True, out_int8=True, inv_s_out=5.0)
+    assert nq.nq_profile_last_kernel() == (10, 2)
+
+
+# ---- quantise and pack in one launch ----------------------------------------------------------------------------
+@pytest.mark.parametrize("N,K", [(1, 4), (8, 60), (31, 64), (33, 68), (65, 1024), (40, 1028), (9, 2048), (32, 2052), (7, 4096),
+                                 (7, 4100), (5, 63)])
+def test_quantise_and_pack_one_launch(nq, N, K):
+    w = inputs.float_weights(N, K, 0.02, seed=N + K)
+    w[0] = 0.0                            # an all-zero channel: scale 1
+    if N > 4:
+        w[3, K // 2] = 3.0e38             # one value decides the scale, the others become zero
+    for n, l, signed in ((8, 2, False), (8, 3, True), (6, 1, False)):
+        wi, s = oracle.quantize(w, n)
+        hi, res = oracle.decompose(wi, n, l, "rtn") if signed else (None, None)
+        if signed:
+            ph_ref = oracle.pack_dense(hi, n - l, oracle.KIND_CARRIER)
+            pl_ref = oracle.pack_dense(oracle.low_encode(res, l, oracle.LOW_SIGNED_L1), l + 1, oracle.KIND_BITSTRING)
+        else:
+            ph_ref, pl_ref = oracle.decompose_pack(wi, n, l)
+        cfg = nq.make_cfg(n, l, nq.NQ_LOW_SIGNED_L1 if signed else nq.NQ_LOW_UNSIGNED_L)
+        ph = torch.full((ph_ref.size + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        pl = torch.full((pl_ref.size + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+        sc = torch.zeros(N + 1, dtype=torch.float32, device="cuda")
+        nq.nq_quantize_decompose_pack(dev(w), N, K, cfg, sc, ph, pl)
+        torch.cuda.synchronize()
+        assert np.array_equal(host(sc)[:N].view(np.uint32), s.view(np.uint32)) and host(sc)[N] == 0.0
+        assert np.array_equal(host(ph)[:ph_ref.size], ph_ref) and np.all(host(ph)[ph_ref.size:] == 0xA5)
+        assert np.array_equal(host(pl)[:pl_ref.size], pl_ref) and np.all(host(pl)[pl_ref.size:] == 0xA5)
