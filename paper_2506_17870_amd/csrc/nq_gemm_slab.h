@@ -8,7 +8,8 @@
 // walks five of its 36 steps.  Weights and activations go straight into the matrix core's operand registers, SL_PD
 // steps ahead: there is too little reuse inside a block to pay for a trip through LDS.  The partial sums meet in LDS
 // (integers: any order), wave 0 runs the epilogue, whose constants and residual codes it has requested before the
-// reduction.  Steps past the end of K are requested out of the buffers' range and are zero.
+// reduction.  A step past the end of K requests the last real weights again; its activations are requested out of the
+// tensor's range, by their vector offset (the range check does not cover the scalar one), and are zero.
 //
 // Activations are fetched with dword-aligned 16-byte buffer loads: any K that is a multiple of four serves as a GEMM.
 // What a row's last piece reads past K belongs to the next row (or is out of range) and meets the zero weights the
@@ -73,11 +74,12 @@ __global__ void __launch_bounds__(64 * NWS, 2) k_nested_gemm_slab(const GemmPara
     uint32_t Q[SL_PD][LP::ARR];
     e_v4i A[SL_PD][2];
     auto request = [&](int slot, int kb) {
-        const int hoff = kb < p.KB ? kb * (H * 256) : NOWHERE;
+        const int kbc = min(kb, p.KB - 1);
+        const int hoff = kbc * (H * 256);
 #pragma unroll
         for (int c = 0; c < (H + 3) / 4; ++c) gb_fetch(P[slot], hrs, H, c, wslot * (4 * H), hoff);
         if constexpr (FULL != 0) {
-            const int loff = kb < p.KB ? kb * (LP::DW * 256) : NOWHERE;
+            const int loff = kbc * (LP::DW * 256);
 #pragma unroll
             for (int c = 0; c < (LP::DW + 3) / 4; ++c) gb_fetch(Q[slot], lrs, LP::DW, c, wslot * (4 * LP::DW), loff);
         }
