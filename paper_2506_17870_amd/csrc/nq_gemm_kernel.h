@@ -33,7 +33,9 @@ constexpr int A_STRIDE = 80;  // bytes per LDS row of the activation tile (64 + 
 
 // FULL: 0 part-bit, 1 full-bit with the unsigned l-bit lower part (concatenation), 2 full-bit with the
 // compensated signed (l+1)-bit lower part (shift-add, Sec. 3.3.3).
-template <int H, int L, int FULL, int EPI, int BM, int BN, int WM, int WN>
+// HALVES: activations in halves of 8 bytes (fast_a == 2).  A kernel of its own: as a third branch of the loads it made the
+// K loop longer for the other two as well (4663 x 6336 -> 20: 178 us with the branch there, 98 us without it).
+template <int H, int L, int FULL, int EPI, int BM, int BN, int WM, int WN, bool HALVES>
 __global__ void __launch_bounds__(256) k_nested_gemm(const GemmParams p)
 {
     static_assert(WM * WN == 4, "four waves per block");
@@ -84,12 +86,7 @@ __global__ void __launch_bounds__(256) k_nested_gemm(const GemmParams p)
         for (int i = 0; i < RPT; ++i) {
             uint4 v = make_uint4(0, 0, 0, 0);
             if (a_ok[i] && k16 < p.K) {
-                if (p.fast_a == 1) {
-                    const int ih = a_ih0[i] + a_kh, iw = a_iw0[i] + a_kw;
-                    if ((unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W)
-                        v = *reinterpret_cast<const uint4 *>(p.x + a_base[i] +
-                                                             ((int64_t)ih * p.W + iw) * p.Cin + a_ci);
-                } else if (p.fast_a == 2) {
+                if constexpr (HALVES) {
                     // eight bytes are inside one pixel: the chunk's halves may lie in two taps
                     int kh = a_kh, kw = a_kw, ci = a_ci;
                     uint2 q[2];
@@ -106,6 +103,11 @@ __global__ void __launch_bounds__(256) k_nested_gemm(const GemmParams p)
                         }
                     }
                     v = make_uint4(q[0].x, q[0].y, q[1].x, q[1].y);
+                } else if (p.fast_a) {
+                    const int ih = a_ih0[i] + a_kh, iw = a_iw0[i] + a_kw;
+                    if ((unsigned)ih < (unsigned)p.H && (unsigned)iw < (unsigned)p.W)
+                        v = *reinterpret_cast<const uint4 *>(p.x + a_base[i] +
+                                                             ((int64_t)ih * p.W + iw) * p.Cin + a_ci);
                 } else {
                     uint32_t w[4] = {0, 0, 0, 0};
                     for (int e = 0; e < 16; ++e) {
@@ -129,7 +131,7 @@ __global__ void __launch_bounds__(256) k_nested_gemm(const GemmParams p)
     };
     auto advance_a = [&]() {
         k16 += 64;
-        if (p.fast_a) {
+        if (HALVES || p.fast_a) {
             a_ci += 64;
             while (a_ci >= p.Cin) {
                 a_ci -= p.Cin;
@@ -264,16 +266,22 @@ inline void launch_timed(F kernel, dim3 grid, dim3 block, size_t lds, hipStream_
         hipLaunchKernelGGL(kernel, grid, block, (uint32_t)lds, st, args...);
 }
 
-#define NQ_LAUNCH_TILE(FULLV, EPIV, BM, BN, WM, WN)                                                       \
-    launch_timed(k_nested_gemm<H, L, FULLV, EPIV, BM, BN, WM, WN>,                                        \
+#define NQ_LAUNCH_TILE(FULLV, EPIV, BM, BN, WM, WN, HALVESV)                                              \
+    launch_timed(k_nested_gemm<H, L, FULLV, EPIV, BM, BN, WM, WN, HALVESV>,                               \
                  dim3((unsigned)((p.M + BM - 1) / BM), (unsigned)((p.N + BN - 1) / BN)), dim3(256), 0, st, \
                  ev_start, ev_stop, p)
 
-#define NQ_LAUNCH_TILES(FULLV, EPIV)                                  \
-    do {                                                              \
-        if (tile == 0) NQ_LAUNCH_TILE(FULLV, EPIV, 256, 64, 4, 1);    \
-        else if (tile == 1) NQ_LAUNCH_TILE(FULLV, EPIV, 128, 256, 1, 4); \
-        else NQ_LAUNCH_TILE(FULLV, EPIV, 64, 256, 1, 4);              \
+#define NQ_LAUNCH_HALVES(FULLV, EPIV, BM, BN, WM, WN)                               \
+    do {                                                                            \
+        if (p.fast_a == 2) NQ_LAUNCH_TILE(FULLV, EPIV, BM, BN, WM, WN, true);       \
+        else NQ_LAUNCH_TILE(FULLV, EPIV, BM, BN, WM, WN, false);                    \
+    } while (0)
+
+#define NQ_LAUNCH_TILES(FULLV, EPIV)                                     \
+    do {                                                                 \
+        if (tile == 0) NQ_LAUNCH_HALVES(FULLV, EPIV, 256, 64, 4, 1);     \
+        else if (tile == 1) NQ_LAUNCH_HALVES(FULLV, EPIV, 128, 256, 1, 4); \
+        else NQ_LAUNCH_HALVES(FULLV, EPIV, 64, 256, 1, 4);               \
     } while (0)
 
 template <int H, int L>
