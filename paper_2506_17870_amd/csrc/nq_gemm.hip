@@ -359,7 +359,7 @@ void fill_params(bool full, const int8_t *d_x, const Geometry &g, const nq_weigh
     else
         p.general = p.acc_dump != nullptr || p.resid != nullptr;
     p.conv_big = 0;
-    p.cin_magic = 0;
+    p.cin_div = 0;
     p.kw_magic = 0;
 }
 
@@ -427,7 +427,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         if (gather && (g.H > 16000 || g.W > 16000 || g.pad > 255 || g.KH > 255 || g.KW > 255)) return NQ_ERR_SHAPE;
         if ((reinterpret_cast<uintptr_t>(d_x) & 3u) != 0) return NQ_ERR_ALIGN;
         p.conv_big = 0;
-        p.cin_magic = 0;
+        p.cin_div = 0;
         p.kw_magic = 0;
         const int WH = (int)ceil_div(w->K, 64 / h);
         const int lf = low_field_bits(&w->cfg);
@@ -439,7 +439,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     }
     if (gs > 0 && gs_out > 0) {
         p.conv_big = 0;
-        p.cin_magic = 0;
+        p.cin_div = 0;
         p.kw_magic = 0;
         const int general = p.general;
         p.general = 1;
@@ -468,7 +468,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         GroupGeom gg;
         if (!plan_grouped(g, gs, 0, w->N, &gg)) return NQ_ERR_UNSUPPORTED;
         p.conv_big = 0;
-        p.cin_magic = 0;
+        p.cin_div = 0;
         p.kw_magic = 65536 / g.KW + 1;      // tap / KW == (tap * kw_magic) >> 16 for the few taps of a filter
         if (!commit()) return NQ_ERR_HIP;
         g_last_family = 7; g_last_variant = 0;
@@ -487,8 +487,10 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     const bool conv_gemm = !plain_gemm && g.Cin % 16 == 0 && aligned16(d_x) &&
                            x_bytes < 0x7fff0000LL && g.M < (int64_t(1) << 31) && g.H <= 8192 && g.W <= 8192 &&
                            g.KH * g.KW * g.KW < 65536 && g.KH <= 15 && g.KW <= 16;
-    p.conv_big = conv_gemm;
-    p.cin_magic = (unsigned)(((uint64_t(1) << 32) + g.Cin - 1) / g.Cin);   // exact below K + 256 for Cin <= 2^15 or one tap
+    const bool cin_pow2 = (g.Cin & (g.Cin - 1)) == 0;
+    p.conv_big = conv_gemm ? (cin_pow2 ? 1 : 2) : 0;
+    // log2(Cin), or the rounded-up reciprocal: exact below K + 256 for Cin <= 2^15 or one tap
+    p.cin_div = cin_pow2 ? (unsigned)__builtin_ctz((unsigned)g.Cin) : (unsigned)(((uint64_t(1) << 32) + g.Cin - 1) / g.Cin);
     p.kw_magic = 65536 / g.KW + 1;
     const bool big_ok = plain_gemm || conv_gemm;
     bool big_wanted = g.M > 64 && w->N > 64 && w->K >= 256;
@@ -496,7 +498,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     // output channels; with 512 channels or more out of 512 in, the large kernel's 256-column tiles win
     // (strided 1x1, 28x28x512 -> 1024 at batch 128: 30 us against 48 us)
     // (the register-stationary kernel takes powers of two only; other channel counts would go to the generic one)
-    if (conv_gemm && (g.Cin & (g.Cin - 1)) == 0 && w->K <= 576 && !(w->K >= 512 && w->N >= 512)) big_wanted = false;
+    if (conv_gemm && cin_pow2 && w->K <= 576 && !(w->K >= 512 && w->N >= 512)) big_wanted = false;
     // Filters over up to 64 output channels at stride 1 go to the windowed kernel (64 channels per block): the
     // large-GEMM kernel's tiles, 128 columns at the least, would be half empty.  (Up to 128 channels they went there
     // too while the large kernel had 256-column tiles only; with its 128 x 128 variant, 3x3, 28x28x128 -> 128 at

@@ -3,8 +3,7 @@
 // serves convolutions: 1x1 stride 1 is a GEMM over the NHWC pixels as it stands, and with CONV
 // any filter over a multiple of 16 input channels, and any GEMM whose K is a multiple of 16 but not of 256 (as a
 // filter of one tap: the test that drops taps past K keeps a row's last pieces out of the next row), is an implicit
-// GEMM in which
-// every 16-byte piece of an activation row is fetched from the input pixel its filter tap points
+// GEMM in which every 16-byte piece of an activation row is fetched from the input pixel its filter tap points
 // at (or from out of range, which reads as zero, for the padding and for the tail of K).
 //
 // Block tile (32*TM) x 256, four waves side by side along N (wave tile 32*TM x 64: TM x 2 MFMA
@@ -91,7 +90,12 @@ __device__ __forceinline__ void gb_fetch(uint32_t *dst, const __amdgpu_buffer_rs
 // TMX: 2..5 = TM; 6 = TM 4 with the compute unit to itself (SOLO: 512 registers, the deep weight pipeline);
 // 7 = TM 4 with one column tile per wave (NARROW: block tile 128 x 128, for layers of up to 128 output channels whose
 // 256-column tile would be half empty; half the registers, so the deep pipeline and the woven K step fit two blocks per unit).
-template <int H, int L, int FULL, int EPI, int TMX, bool CONV>
+// CONV: 0 GEMM, 1 implicit GEMM over a power-of-two number of channels, 2 over any other multiple of 16 (or a K that is
+// no multiple of 256).  The power of two has a kernel of its own: the tap of a piece is a shift there, and with the
+// multiplications of the general form in its place the kernels needed 3 to 13 registers more, three of them spilled, and
+// every filter layer paid (784 x 4608 -> 768 29.4 us against 31.0 us, a 14 x 14 x 1024 bottleneck at batch 64 36.6 us
+// against 37.2 us).
+template <int H, int L, int FULL, int EPI, int TMX, int CONV>
 __global__ void __launch_bounds__(256, ((TMX <= 4 || TMX == 7) && EPI != EPI_ANY ? 2 : 1)) k_nested_gemm_big(const GemmParams p)
 {
     constexpr int TM = TMX >= 6 ? 4 : TMX;
@@ -213,9 +217,10 @@ __global__ void __launch_bounds__(256, ((TMX <= 4 || TMX == 7) && EPI != EPI_ANY
 #pragma unroll
         for (int par = 0; par < 4; ++par) {
             const int kk = it * (GB_KI * 64) + 16 * piece[par];
-            const int tap = (int)__umulhi((unsigned)kk, p.cin_magic), ci = kk - __mul24(tap, p.Cin);
+            const int tap = CONV == 1 ? kk >> p.cin_div : (int)__umulhi((unsigned)kk, p.cin_div);
+            const int ci = CONV == 1 ? kk & (p.Cin - 1) : kk - __mul24(tap, p.Cin);
             const int kh = __mul24(tap, p.kw_magic) >> 16, kw = tap - __mul24(kh, p.KW);
-            tap_off[par] = __mul24(__mul24(kh, p.W) + kw, p.Cin) + ci;
+            tap_off[par] = (CONV == 1 ? (__mul24(kh, p.W) + kw) << p.cin_div : __mul24(__mul24(kh, p.W) + kw, p.Cin)) + ci;
             // the tap's bits in a pixel's table entry; a piece past the end of K gets bit 15, which no pixel has
             tap_hw[par] = kk < p.K ? (int)((1u << kh) | (0x10000u << kw)) : 0x8000;
         }
@@ -668,10 +673,12 @@ void launch_nested_gemm_big(bool full, const GemmParams &p, int tm_forced, int *
         else NQ_GB_TM(FULLV, EPI_F32, CONVV);                            \
     } while (0)
     const int fmode = full ? (p.low_signed ? 2 : 1) : 0;
-    if (p.conv_big) {
-        if (fmode == 2) NQ_GB_MODE(2, true); else if (fmode == 1) NQ_GB_MODE(1, true); else NQ_GB_MODE(0, true);
+    if (p.conv_big == 2) {
+        if (fmode == 2) NQ_GB_MODE(2, 2); else if (fmode == 1) NQ_GB_MODE(1, 2); else NQ_GB_MODE(0, 2);
+    } else if (p.conv_big) {
+        if (fmode == 2) NQ_GB_MODE(2, 1); else if (fmode == 1) NQ_GB_MODE(1, 1); else NQ_GB_MODE(0, 1);
     } else {
-        if (fmode == 2) NQ_GB_MODE(2, false); else if (fmode == 1) NQ_GB_MODE(1, false); else NQ_GB_MODE(0, false);
+        if (fmode == 2) NQ_GB_MODE(2, 0); else if (fmode == 1) NQ_GB_MODE(1, 0); else NQ_GB_MODE(0, 0);
     }
 }
 

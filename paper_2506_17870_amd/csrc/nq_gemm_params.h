@@ -23,9 +23,10 @@ struct GemmParams {
     int relu, out_int8, fast_a;
     int low_signed;   // lower-bit page holds signed fields of l + 1 bits (compensated format)
     int general;   // 1: the element-wise epilogue is needed (set by the host from the arguments)
-    // implicit GEMM of the large-GEMM kernel: k / Cin = umulhi(k, cin_magic), tap / KW = (tap * kw_magic) >> 16
+    // implicit GEMM of the large-GEMM kernel: conv_big 1: Cin = 2^cin_div; 2: k / Cin = umulhi(k, cin_div);
+    // tap / KW = (tap * kw_magic) >> 16
     int conv_big;
-    unsigned cin_magic;
+    unsigned cin_div;
     int kw_magic;
 };
 
