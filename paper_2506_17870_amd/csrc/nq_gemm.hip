@@ -516,7 +516,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     // blocks, K = 4096: 15.7 against 20.6) or short (400 blocks, K = 256: 4.8 against 9.5), and behind in between (384
     // blocks, K = 768: 9.0 against 8.3).  Up to 32 rows, and up to 64 with more blocks than units, the kernel for few
     // rows has the same split and reads the weights once (16 x 1024 -> 4096: 4.1 against 4.8; 64 x 512 -> 512 the other
-    // way round, 4.8 against 4.1).  A single K step leaves three of four waves without work and is not taken.
+    // way round, 4.8 against 4.1).  A single K step is left to the kernels below, whose rule for what remains includes it.
     const bool slab_fits = slab_ok(g, d_x, w->K, x_bytes, p.general != 0);
     const bool skinny_ok = g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0 && g.M <= 64 && w->K % 16 == 0 &&
                            aligned16(d_x) && ceil_div(w->N, 32) <= 0x7fffffffLL;
@@ -585,10 +585,13 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         NQ_DISPATCH_HL(h, l, launch_nested_conv_window, full, 0, p, wg, lds, s, ev0, ev1);
         return launch_status();
     }
-    // What is left would go to the generic kernel, whose 128 x 256 tiles walk K one step at a time: small blocks again,
-    // up to the number at which both take as long (K = 1000, N = 1000: 1600 blocks 13.0 us against 23.8, 3200 blocks 23.0
-    // against 24.7; K = 200, N = 2048: 832 blocks 7.4 against 9.9, 1600 blocks 11.2 against 9.9).
-    if (slab_fits && force == 0 && slab_blocks <= (w->K >= 512 ? 2560 : 1024)) return run_slab();
+    // What is left would go to the generic kernel, which walks K one step at a time: small blocks again, up to the number
+    // at which both take as long.  Both sides measured on N = 16 to 1000, time against the generic kernel's, worst of
+    // them at the limit and at the next number up: K = 16 to 96 0.9 to 1.0 at 512 blocks, 1.3 at 640; K = 144 to 256 0.93
+    // at 768, 1.2 at 900; K = 328 to 640 0.90 at 1280, 1.17 at 1600; K = 776 to 2008 0.95 at 2048, 1.2 at 2500.  (A single K
+    // step leaves three of four waves without work, and up to 512 blocks that costs nothing: the launch is what takes 4 us.)
+    const int64_t slab_limit = w->K <= 128 ? 512 : (w->K < 320 ? 768 : (w->K < 768 ? 1280 : 2048));
+    if (slab_fits && force == 0 && slab_blocks <= slab_limit) return run_slab();
     const int tile = pick_tile(g.M, w->N);
     if (ceil_div(g.M, NQ_TILE_BM[tile]) > 0x7fffffffLL || ceil_div(w->N, NQ_TILE_BN[tile]) > 65535)
         return NQ_ERR_SHAPE;

@@ -103,6 +103,23 @@ def test_small_outputs_by_the_library(nq):
     forced(nq, make_case(nq, 256, 2304, 8, 2, seed=2), inputs.uniform_activations((1, 14, 14, 256), seed=2), (3, 3, 1, 1), "", 11)
 
 
+@pytest.mark.parametrize("M,N,K,i8,family", [
+    # what no other kernel wants: small blocks up to the number at which the generic kernel takes as long, per length of K
+    (8192, 64, 48, True, 11), (8224, 64, 48, True, 1), (3136, 256, 32, False, 1), (16384, 32, 96, False, 11),
+    (12256, 64, 144, True, 11), (12320, 64, 144, True, 1), (29008, 32, 192, True, 1), (20480, 64, 520, False, 11),
+    (20512, 64, 520, False, 1), (32768, 64, 776, True, 11), (32800, 64, 776, True, 1)])
+def test_small_outputs_instead_of_the_generic_kernel(nq, M, N, K, i8, family):
+    case = make_case(nq, N, K, 8, 2, seed=M + K)
+    x = inputs.uniform_activations((M, K), seed=K)
+    epi, _, okw = epi_pair(nq, case, True, (M,), dump=False, s_a=0.02, out_int8=i8, inv_s_out=4.0)
+    y = torch.full((M, N), 77, dtype=torch.int8 if i8 else torch.float32, device="cuda")
+    nq.nq_gemm_full(dev(x), M, case.W.desc, epi, y)
+    torch.cuda.synchronize()
+    assert nq.nq_profile_last_kernel()[0] == family
+    acc = oracle.gemm_acc(x, case.ow_full)
+    check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, i8)
+
+
 # ---- short reductions in steps of 16, activations in steps of 8 ------------------------------------------------
 @pytest.mark.parametrize("M,N,K", [(100, 64, 16), (333, 96, 32), (333, 144, 48), (4097, 192, 96), (129, 272, 144),
                                    (700, 64, 192), (257, 40, 240)])
