@@ -516,13 +516,16 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     // blocks, K = 4096: 15.7 against 20.6) or short (400 blocks, K = 256: 4.8 against 9.5), and behind in between (384
     // blocks, K = 768: 9.0 against 8.3).  Up to 32 rows, and up to 64 with more blocks than units, the kernel for few
     // rows has the same split and reads the weights once (16 x 1024 -> 4096: 4.1 against 4.8; 64 x 512 -> 512 the other
-    // way round, 4.8 against 4.1).  A single K step is left to the kernels below, whose rule for what remains includes it.
+    // way round, 4.8 against 4.1).  So it does for 12 to 16 K steps: two rounds of eight waves here, which the four-step
+    // pipeline runs as four (33 to 64 rows, K = 720 to 1024: 4.2 to 4.8 there, 4.6 to 5.2 here; K = 704 and 1088 are ahead here).
+    // A single K step is left to the kernels below, whose rule for what remains includes it.
     const bool slab_fits = slab_ok(g, d_x, w->K, x_bytes, p.general != 0);
     const bool skinny_ok = g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0 && g.M <= 64 && w->K % 16 == 0 &&
                            aligned16(d_x) && ceil_div(w->N, 32) <= 0x7fffffffLL;
     const int64_t slab_blocks = ceil_div(g.M, 32) * ceil_div(w->N, 32);
     const bool slab_wanted = (slab_blocks <= 256 || (slab_blocks <= 512 && (w->K <= 512 || w->K >= 2048))) &&
-                             w->K > 64 && !(skinny_ok && w->K >= 256 && (g.M <= 32 || slab_blocks > 256));
+                             w->K > 64 &&
+                             !(skinny_ok && w->K >= 256 && (g.M <= 32 || slab_blocks > 256 || (p.KB >= 12 && p.KB <= 16)));
     auto run_slab = [&]() {
         if (!commit()) return NQ_ERR_HIP;
         g_last_family = 11; g_last_variant = 0;

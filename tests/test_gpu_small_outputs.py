@@ -107,8 +107,10 @@ def test_small_outputs_by_the_library(nq):
     # what no other kernel wants: small blocks up to the number at which the generic kernel takes as long, per length of K
     (8192, 64, 48, True, 11), (8224, 64, 48, True, 1), (3136, 256, 32, False, 1), (16384, 32, 96, False, 11),
     (12256, 64, 144, True, 11), (12320, 64, 144, True, 1), (29008, 32, 192, True, 1), (20480, 64, 520, False, 11),
-    (20512, 64, 520, False, 1), (32768, 64, 776, True, 11), (32800, 64, 776, True, 1)])
-def test_small_outputs_instead_of_the_generic_kernel(nq, M, N, K, i8, family):
+    (20512, 64, 520, False, 1), (32768, 64, 776, True, 11), (32800, 64, 776, True, 1),
+    # up to 64 rows: the kernel for few rows where its split has the fewer idle rounds
+    (33, 256, 704, False, 11), (33, 256, 720, False, 6), (64, 96, 1024, True, 6), (40, 96, 1040, False, 11), (32, 96, 512, False, 6)])
+def test_small_outputs_where_they_are_the_faster_kernel(nq, M, N, K, i8, family):
     case = make_case(nq, N, K, 8, 2, seed=M + K)
     x = inputs.uniform_activations((M, K), seed=K)
     epi, _, okw = epi_pair(nq, case, True, (M,), dump=False, s_a=0.02, out_int8=i8, inv_s_out=4.0)
