@@ -194,17 +194,14 @@ void launch_nested_conv_grouped_mid(bool full, const GemmParams &p, const GroupG
     const size_t lds = (size_t)g.lds_bytes;
     // 16-byte stores need half tiles that start on multiples of 16 channels
     const bool vec = epi_mode(p) == EPI_I8 && g.hout % 16 == 0;
-#define NQ_GM_LAUNCH(FULLV, EPIV)                                                                                   \
-    do {                                                                                                            \
-        if (g.taps == 1)                                                                                            \
-            launch_timed(k_nested_conv_grouped_mid<H, L, FULLV, EPIV, 1>, grid, block, lds, st, ev_start, ev_stop, p, g); \
-        else                                                                                                        \
-            launch_timed(k_nested_conv_grouped_mid<H, L, FULLV, EPIV, 9>, grid, block, lds, st, ev_start, ev_stop, p, g); \
-    } while (0)
-#define NQ_GM_MODES(FULLV)                          \
-    do {                                            \
-        if (vec) NQ_GM_LAUNCH(FULLV, EPI_I8);       \
-        else NQ_GM_LAUNCH(FULLV, EPI_ANY);          \
+#define NQ_GM_LAUNCH(FULLV, EPIV, NTV) \
+    launch_timed(k_nested_conv_grouped_mid<H, L, FULLV, EPIV, NTV>, grid, block, lds, st, ev_start, ev_stop, p, g)
+    // (a single tap comes here with 16-byte stores only: the caller leaves the others to the direct kernel)
+#define NQ_GM_MODES(FULLV)                               \
+    do {                                                 \
+        if (g.taps == 1) NQ_GM_LAUNCH(FULLV, EPI_I8, 1); \
+        else if (vec) NQ_GM_LAUNCH(FULLV, EPI_I8, 9);    \
+        else NQ_GM_LAUNCH(FULLV, EPI_ANY, 9);            \
     } while (0)
     if (full && p.low_signed) NQ_GM_MODES(2); else if (full) NQ_GM_MODES(1); else NQ_GM_MODES(0);
 }

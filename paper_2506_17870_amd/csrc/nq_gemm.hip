@@ -449,9 +449,15 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         if (ceil_div(g.M, 32) > 0x7fffffffLL || ceil_div(w->N, 64) > 65535) return NQ_ERR_SHAPE;
         // Groups of up to 32 channels, whole dwords of input channels, up to nine taps (what a wave holds in registers):
         // on the matrix cores (32 x 56 x 56 x 256, 32 groups of 8: 24 us against 218 us).  Other widths, filters and
-        // alignments stay with the direct kernel.
+        // alignments stay with the direct kernel, and so do short sums, whose time is the way in and out: up to K = 36
+        // with outputs that leave byte by byte or as fp32 (K = 8 to 16: 87 of 97 shapes slower here, up to 24.4 us against
+        // 45.0; K = 33 to 36: up to 200 against 245; from K = 40 on none of 408 is), up to K = 8 with 16-byte stores below
+        // a million outputs (4.2 against 4.8; beyond, 1x1 over 28 x 28 x 128 in 16 groups at batch 32, 11.9 against 5.2).
+        const int widest = gs > gs_out ? gs : gs_out;
+        const bool wide_out = widest <= 32 && !general && p.out_int8 && 32 / widest * gs_out % 16 == 0;
+        const bool mid_wanted = w->K > 36 || (wide_out && (w->K > 8 || g.M * w->N >= (int64_t(1) << 20)));
         GroupGeom mg;
-        if (quads && gs <= 32 && gs_out <= 32 && g.KH * g.KW <= 9 && plan_grouped(g, gs, gs_out, w->N, &mg)) {
+        if (mid_wanted && quads && widest <= 32 && g.KH * g.KW <= 9 && plan_grouped(g, gs, gs_out, w->N, &mg)) {
             p.general = general;
             p.kw_magic = 65536 / g.KW + 1;
             if (!commit()) return NQ_ERR_HIP;

@@ -188,3 +188,27 @@ def test_resnext_and_shufflenet_layers_reduced_batch(nq):
         for full in (True, False):
             run_gconv_both(nq, case, x, (KH, KH, stride, pad), groups, full, s_a=0.02, bias=bias, relu=True, out_int8=True,
                            inv_s_out=5.0)
+
+
+@pytest.mark.parametrize("geom,int8,variant", [
+    # B, H, W, Cin, Cout, groups, KH, stride, pad: short sums stay with the direct kernel (1, 0: by bytes) unless the
+    # matrix-core kernel (2) can store sixteen channels at a time
+    ((1, 9, 8, 64, 64, 8, 1, 1, 0), False, 1),     # 1x1 over 8 channels, fp32
+    ((1, 9, 8, 64, 64, 8, 1, 1, 0), True, 1),      # int8, but few outputs
+    ((2, 96, 96, 64, 64, 8, 1, 1, 0), True, 2),    # over a million outputs
+    ((1, 9, 8, 48, 48, 3, 1, 1, 0), True, 2),      # 16 channels
+    ((1, 9, 8, 48, 48, 3, 1, 1, 0), False, 1),
+    ((1, 9, 8, 48, 36, 3, 1, 1, 0), True, 1),      # outputs that fill no 16-byte store
+    ((1, 9, 8, 24, 24, 2, 1, 1, 0), True, 1),      # 12 channels: half tiles of 24
+    ((1, 8, 9, 64, 96, 16, 3, 1, 1), False, 1),    # 3x3 over 4 channels, K = 36
+    ((1, 8, 9, 64, 128, 16, 3, 1, 1), True, 2),
+    ((1, 8, 9, 40, 40, 4, 2, 1, 1), False, 0),     # 10 channels: no dwords
+    ((1, 8, 9, 48, 48, 4, 2, 1, 1), False, 2),     # 12 channels, K = 48
+])
+def test_which_grouped_kernel_runs(nq, geom, int8, variant):
+    B, H, W, Cin, Cout, groups, KH, stride, pad = geom
+    case = make_case(nq, Cout, KH * KH * (Cin // groups), 8, 2, seed=sum(geom))
+    x = inputs.uniform_activations((B, H, W, Cin), seed=Cin + H)
+    kw = dict(out_int8=True, inv_s_out=5.0) if int8 else {}
+    run_gconv_both(nq, case, x, (KH, KH, stride, pad), groups, True, s_a=0.02, **kw)
+    assert nq.nq_profile_last_kernel() == (10, variant)
