@@ -190,6 +190,52 @@ def test_resnext_and_shufflenet_layers_reduced_batch(nq):
                            inv_s_out=5.0)
 
 
+def compensated_case(nq, C, K, n, l, seed):
+    from oracle import nq_oracle as oracle
+    case = make_case(nq, C, K, n, l, seed)
+    case.cfg = nq.make_cfg(n, l, nq.NQ_LOW_SIGNED_L1)
+    case.W = nq.NestedWeight.from_int8(dev(case.w_int), dev(case.scale), case.cfg)
+    case.ow_part = oracle.decompose(case.w_int, n, l, "rtn")[0].astype(np.int16)
+    case.ow_full = case.w_int.astype(np.int16)
+    return case
+
+
+@pytest.mark.parametrize("geom", [
+    # B, H, W, Cin, Cout, groups, KH, stride, pad: whole dwords that the matrix-core kernels do not take
+    (1, 7, 6, 128, 128, 2, 3, 1, 1),      # 64 channels per group
+    (1, 9, 7, 128, 64, 2, 3, 2, 1),       # ... at stride 2, half as many outputs
+    (1, 6, 7, 16, 80, 2, 3, 1, 1),        # 8 in, 40 out
+    (1, 8, 7, 24, 24, 3, 5, 1, 2),        # 25 taps
+    (2, 5, 6, 16, 16, 1, 4, 2, 1),        # 16 taps, even filter, stride 2
+])
+def test_direct_kernel_by_dwords(nq, geom):
+    B, H, W, Cin, Cout, groups, KH, stride, pad = geom
+    K = KH * KH * (Cin // groups)
+    Ho, Wo = (H + 2 * pad - KH) // stride + 1, (W + 2 * pad - KH) // stride + 1
+    x = inputs.uniform_activations((B, H, W, Cin), seed=Cin + H)
+    bias = inputs.small_floats(Cout, 0.1, seed=3)
+    res = inputs.uniform_activations((B, Ho, Wo, Cout), seed=Cout)
+    for make, n, l in ((make_case, 8, 3), (compensated_case, 6, 2)):
+        case = make(nq, Cout, K, n, l, seed=sum(geom))
+        for full in (True, False):
+            run_gconv_both(nq, case, x, (KH, KH, stride, pad), groups, full, s_a=0.02)
+            assert nq.nq_profile_last_kernel() == (10, 1)
+            run_gconv_both(nq, case, x, (KH, KH, stride, pad), groups, full, s_a=0.02, bias=bias, residual=res, s_r=0.04,
+                           relu=True, out_int8=True, inv_s_out=5.0)
+            assert nq.nq_profile_last_kernel() == (10, 1)
+
+
+@pytest.mark.parametrize("n,l", [(8, l) for l in range(1, 7)] + [(6, l) for l in range(1, 5)])
+@pytest.mark.parametrize("make", [make_case, compensated_case])
+def test_direct_kernel_by_dwords_every_nesting(nq, make, n, l):
+    B, H, W, Cin, Cout, groups, KH = 1, 7, 6, 16, 80, 2, 3
+    case = make(nq, Cout, KH * KH * (Cin // groups), n, l, seed=10 * n + l)
+    x = inputs.uniform_activations((B, H, W, Cin), seed=l) >> (8 - n)
+    for full in (True, False):
+        run_gconv_both(nq, case, x, (KH, KH, 2, 1), groups, full, s_a=0.02, relu=True)
+        assert nq.nq_profile_last_kernel() == (10, 1)
+
+
 @pytest.mark.parametrize("geom,int8,variant", [
     # B, H, W, Cin, Cout, groups, KH, stride, pad: short sums stay with the direct kernel (1, 0: by bytes) unless the
     # matrix-core kernel (2) can store sixteen channels at a time
