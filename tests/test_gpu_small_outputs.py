@@ -154,6 +154,36 @@ def test_large_kernel_any_multiple_of_sixteen(nq, choice):
                (k, k, stride, pad), choice, 4)
 
 
+@pytest.mark.parametrize("M,N,K,family", [
+    (300, 130, 624, 1), (300, 130, 656, 4), (200, 258, 752, 1), (200, 258, 784, 4), (12416, 258, 784, 1), (300, 500, 656, 4),
+    (300, 130, 1024, 4)])
+def test_large_kernel_with_ragged_outputs(nq, M, N, K, family):
+    # the element-wise epilogue: long reductions, filled column tiles or few blocks; K = 1024 is the plain form
+    case = make_case(nq, N, K, 8, 2, seed=K)
+    x = inputs.uniform_activations((M, K), seed=M)
+    epi, _, okw = epi_pair(nq, case, True, (M,), dump=False, s_a=0.02, out_int8=True, inv_s_out=4.0)
+    y = torch.full((M, N), 77, dtype=torch.int8, device="cuda")
+    nq.nq_gemm_full(dev(x), M, case.W.desc, epi, y)
+    torch.cuda.synchronize()
+    assert nq.nq_profile_last_kernel()[0] == family
+    acc = oracle.gemm_acc(x, case.ow_full)
+    check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, True)
+
+
+@pytest.mark.parametrize("Cin,family", [(192, 2), (320, 4), (384, 2), (448, 4), (176, 4)])
+def test_large_kernel_or_windows_with_ragged_outputs(nq, Cin, family):
+    x = inputs.uniform_activations((1, 12, 13, Cin), seed=Cin)
+    case = make_case(nq, 72, 9 * Cin, 8, 2, seed=Cin)
+    cs = nq.nq_conv_shape(1, 12, 13, Cin, 72, 3, 3, 1, 1)
+    epi, _, okw = epi_pair(nq, case, True, (1, 12, 13), dump=False, s_a=0.02, out_int8=True, inv_s_out=4.0)
+    y = torch.full((1, 12, 13, 72), 77, dtype=torch.int8, device="cuda")
+    nq.nq_conv_full(dev(x), cs, case.W.desc, epi, y)
+    torch.cuda.synchronize()
+    assert nq.nq_profile_last_kernel()[0] == family
+    acc = oracle.conv_acc(x, case.ow_full.reshape(72, 3, 3, Cin), 1, 1)
+    check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, True)
+
+
 # ---- groups of up to 32 channels ------------------------------------------------------------------------------
 @pytest.mark.parametrize("geom", [
     # B, H, W, Cin, Cout, groups, KH, stride, pad
