@@ -555,9 +555,12 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     StatGeom tg;
     // (a K other than 64, 128 or 256 pays for its panels' padding: ahead of the generic kernel on many rows, 78400 x 32 ->
     // 128: 9.6 us against 18.0, 313600 x 16 -> 64: 14.2 against 17.4, and behind it on few rows or few columns, 19600 x 32
-    // -> 256: 8.4 against 7.0, 78400 x 144 -> 64: 14.1 against 9.6)
+    // -> 256: 8.4 against 7.0, 78400 x 144 -> 64: 14.1 against 9.6.  Above K = 128 the panels are padded to 256 bytes and it
+    // takes 100000 rows: 60000 x 192 -> 256 16.2 there against 18.7 here.  The element-wise epilogue is behind throughout:
+    // 60000 x 96 -> 172 42.1 there against 45.6 here.)
     const bool stat_wanted = w->K == 64 || w->K == 128 || w->K == 256 ||
-                             (g.M >= 40000 && (w->N > 64 || (g.M >= 200000 && w->K <= 64)));
+                             (!p.general && g.M >= (w->K <= 128 ? 40000 : 100000) &&
+                              (w->N > 64 || (g.M >= 200000 && w->K <= 64)));
     if ((force == 9 || (force == 0 && g.M > 64 && stat_wanted)) && plan_stat(g, d_x, w->N, w->K, &tg)) {
         if (!commit()) return NQ_ERR_HIP;
         g_last_family = 9; g_last_variant = tg.wn;

@@ -136,6 +136,21 @@ def test_stationary_weights_strided_short_reduction(nq):
     forced(nq, make_case(nq, 96, 48, 8, 3, seed=3), x, (1, 1, 2, 0), "9", 9)
 
 
+@pytest.mark.parametrize("M,N,K,family", [(40000, 80, 48, 9), (39999, 80, 48, 1), (40000, 72, 48, 1), (90000, 80, 144, 1),
+                                          (100000, 80, 144, 9), (40000, 72, 64, 9)])
+def test_stationary_weights_by_the_library(nq, M, N, K, family):
+    # lengths that are no power of two: many rows, more of them above K = 128, and sixteen channels per store
+    case = make_case(nq, N, K, 8, 2, seed=K)
+    x = inputs.uniform_activations((M, K), seed=N)
+    epi, _, okw = epi_pair(nq, case, True, (M,), dump=False, s_a=0.02, out_int8=True, inv_s_out=4.0)
+    y = torch.full((M, N), 77, dtype=torch.int8, device="cuda")
+    nq.nq_gemm_full(dev(x), M, case.W.desc, epi, y)
+    torch.cuda.synchronize()
+    assert nq.nq_profile_last_kernel()[0] == family
+    acc = oracle.gemm_acc(x, case.ow_full)
+    check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, True)
+
+
 @pytest.mark.parametrize("Cin,k,stride,pad", [(8, 3, 1, 1), (24, 3, 2, 1), (40, 1, 1, 0), (72, 5, 1, 2)])
 def test_activations_in_steps_of_eight(nq, Cin, k, stride, pad):
     x = inputs.uniform_activations((2, 9, 10, Cin), seed=Cin)
