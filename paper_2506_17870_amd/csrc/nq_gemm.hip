@@ -195,7 +195,6 @@ bool plan_grouped(const Geometry &g, int gs, int gs_out, int64_t C, GroupGeom *g
     if (best < 0.0) return false;
     gg->gs = gs;
     gg->gs_out = gs_out; gg->hin = per_half * gs; gg->hout = per_half * gs_out;
-    gg->images = (int)images;
     gg->taps = g.KH * g.KW;
     gg->CT = CT;
     gg->R = bR; gg->CW = bCW;

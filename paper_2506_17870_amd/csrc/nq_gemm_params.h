@@ -85,9 +85,6 @@ struct SmallCinGeom {
 // one image).
 struct GroupGeom {
     int gs;           // channels per group (1, 2 or 4), inputs and outputs alike; nq_conv_grouped_mid.h: input channels
-    int gs_out;       // nq_conv_grouped_mid.h only: output channels per group, input and output channels of a half tile
-    int hin, hout;    // (its whole groups); 0 otherwise
-    int images;       // B
     int taps;         // KH * KW (<= 28; nq_conv_grouped_mid.h: <= 9)
     int CT;           // channel tiles: ceil(C / 64), or pairs of half tiles
     int R, CW;        // output rows and columns of a patch
@@ -103,6 +100,8 @@ struct GroupGeom {
     int lds_bytes;    // dynamic LDS of the kernel
     int grid_x;       // persistent blocks per channel tile
     int64_t x_bytes;  // B * H * W * C (< 2^31)
+    int gs_out;       // nq_conv_grouped_mid.h only: output channels per group, input and output channels of a half tile
+    int hin, hout;    // (its whole groups); 0 otherwise
 };
 
 // Geometry of the stationary-weights GEMM (1x1 convolutions with 64, 128 or 256 input channels at any stride,
