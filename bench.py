@@ -47,7 +47,8 @@ TRAFFIC = {   # profiles/gemm_big_conv3x3_b128_counters.txt: FETCH_SIZE x 1.999 
 }
 KERNEL_SOURCES = ("nq_gemm_big.h", "nq_epilogue.h", "nq_codec.h", "nq_gemm_kernel.h")   # what k_nested_gemm_big is made of
 FAMILY = {1: "k_nested_gemm", 2: "k_nested_conv_window", 3: "k_nested_conv_rowstream", 4: "k_nested_gemm_big",
-          5: "k_nested_conv_smallcin", 6: "k_nested_gemm_skinny", 7: "k_nested_conv_grouped", 8: "k_nested_gemm_words", 9: "k_nested_gemm_stat"}
+          5: "k_nested_conv_smallcin", 6: "k_nested_gemm_skinny", 7: "k_nested_conv_grouped", 8: "k_nested_gemm_words", 9: "k_nested_gemm_stat",
+          10: "k_nested_conv_grouped_mid / _any", 11: "k_nested_gemm_slab"}
 
 
 def kernel_sources_digest():
@@ -112,7 +113,7 @@ def stamped_forward(model, binding, dx, s_x, full):
             byts = x_bytes + pages + out_bytes + (m * wd.N if epi.d_residual else 0) + 8 * wd.N
             if epi.d_residual:
                 layer += " + residual"
-            inst = FAMILY.get(fam, "?") + f"<{h_bits},{l_bits},{'full' if full else 'part'}"
+            inst = FAMILY[fam] + f"<{h_bits},{l_bits},{'full' if full else 'part'}"
             if fam == 4:
                 inst += f",{'int8' if epi.out_int8 else 'fp32'} out,TM={var},{'filter' if filt else 'plain'}"
             if fam == 9:

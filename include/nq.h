@@ -334,9 +334,10 @@ nq_status nq_conv_part(const int8_t *d_x, const nq_conv_shape *shape, const nq_w
  * Dense pages only (NQ_ERR_UNSUPPORTED for the word layout); groups must divide both channel counts and d_x be
  * smaller than 2 GiB (NQ_ERR_SHAPE).  Three kernels: depthwise layers and groups of 2 or 4 channels with
  * Cin == Cout a multiple of 16, up to 28 taps and a 16-byte aligned d_x, and groups of up to 32 input and 32 output
- * channels in whole dwords (gs, Cin multiples of 4, 4-byte aligned d_x) with up to 9 taps, run on the matrix cores; every
- * other shape (still wider groups, odd channel counts, any alignment) runs as a direct convolution on the vector ALU:
- * same results, about a tenth of the speed. */
+ * channels in whole dwords (gs, Cin multiples of 4, 4-byte aligned d_x) with up to 9 taps and sums long enough for it to
+ * pay (K above 36; with int8 outputs in whole 16-byte stores K above 8, or a million outputs), run on the matrix cores; every other shape
+ * (still wider groups, short sums, odd channel counts, any alignment) runs as a direct convolution on the vector ALU:
+ * same results, for long sums at about a tenth of the speed. */
 nq_status nq_gconv_full(const int8_t *d_x, const nq_conv_shape *shape, int groups, const nq_weight *w,
                         const nq_epilogue *epi, void *d_y, void *stream);
 nq_status nq_gconv_part(const int8_t *d_x, const nq_conv_shape *shape, int groups, const nq_weight *w,
@@ -364,9 +365,10 @@ nq_status nq_set_tuning(int key, int value);
 nq_status nq_profile_next_launch(void *start_event, void *stop_event);
 /* Profiling aid: which kernel the last nq_gemm_* / nq_conv_* / nq_gconv_* launch of this host thread ran:
  * *family as in NQ_TUNE_KERNEL (7 = depthwise / grouped on the matrix cores, 8 = word pages, 10 = other
- * grouped convolutions; 0 before the first launch), *variant 2 for wider groups on the matrix cores (family 10), the tile height of the large-GEMM kernel (2..6), the tile shape of the generic kernel, the waves along N
- * of the stationary-weights GEMM, else 0.  Lets a
- * benchmark group its time stamps by kernel instantiation, as a kernel trace does.  Either pointer may be NULL. */
+ * grouped convolutions; 0 before the first launch), *variant for family 10: 2 wider groups on the matrix cores, 1 or 0
+ * the direct kernel by dwords or by bytes; else the tile height of the large-GEMM kernel (2..7), the tile shape of the
+ * generic kernel, the waves along N of the stationary-weights GEMM, else 0.  Lets a benchmark group its time stamps by
+ * kernel instantiation, as a kernel trace does.  Either pointer may be NULL. */
 nq_status nq_profile_last_kernel(int *family, int *variant);
 /* Timing events for the call above: create / destroy a hipEvent_t, and the milliseconds
  * between two completed events (blocks until stop_event has completed). */

@@ -32,7 +32,7 @@ thread_local void *g_ev_stop = nullptr;
 std::atomic<int> g_tune[NQ_TUNE_COUNT];
 
 // What the last launch of this thread ran (nq_profile_last_kernel): kernel family as in NQ_TUNE_KERNEL
-// (7 = depthwise / grouped, 8 = word pages, 9 = stationary-weights GEMM) and, for the large-GEMM kernel, its tile height.
+// (7 = depthwise / grouped, 8 = word pages, 10 = other grouped convolutions) and, for the large-GEMM kernel, its tile height.
 thread_local int g_last_family = 0;
 thread_local int g_last_variant = 0;
 
@@ -387,7 +387,8 @@ bool wait_for_page(const nq_weight *w, hipStream_t s)
 // gs: 0 for a GEMM or a dense convolution, else the channels per group of a grouped convolution
 // (the caller has checked that the shape is one the grouped kernel takes).
 // gs_out: 0, or the output channels per group of a grouped convolution that the kernel for 1, 2 or 4 channels per
-// group does not take (then gs is the input channels per group, and the direct kernel runs).
+// group does not take (then gs is the input channels per group, and the kernel for up to 32 channels per group or the
+// direct one runs).
 nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *w, const nq_epilogue *epi,
               void *d_y, void *stream, int gs = 0, int gs_out = 0)
 {
@@ -535,7 +536,9 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     // rows has the same split and reads the weights once (16 x 1024 -> 4096: 4.1 against 4.8; 64 x 512 -> 512 the other
     // way round, 4.8 against 4.1).  So it does for 12 to 16 K steps: two rounds of eight waves here, which the four-step
     // pipeline runs as four (33 to 64 rows, K = 720 to 1024: 4.2 to 4.8 there, 4.6 to 5.2 here; K = 704 and 1088 are ahead here).
-    // A single K step is left to the kernels below, whose rule for what remains includes it.
+    // A single K step is left to the kernels below, whose rule for what remains includes it.  The limit of 512 blocks is that of
+    // the large kernel's plain form; against its gathering form they are ahead further (6272 x 864 -> 96, 3x3, 588 blocks: 6.1
+    // against 8.4; 1000 x 1008 -> 1008, 1024 blocks: 8.0 against 9.6), which the rule does not use.
     const bool slab_fits = slab_ok(g, d_x, w->K, x_bytes, p.general != 0);
     const bool skinny_ok = g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0 && g.M <= 64 && w->K % 16 == 0 &&
                            aligned16(d_x) && ceil_div(w->N, 32) <= 0x7fffffffLL;
@@ -792,7 +795,7 @@ nq_status gconv(bool full, const int8_t *d_x, const nq_conv_shape *sh, int group
     if (sh->H + 2 * sh->pad < sh->KH || sh->W + 2 * sh->pad < sh->KW) return NQ_ERR_SHAPE;
     // what the matrix-core kernel is built for: as many output as input channels, groups inside a run of 4
     // channels, 16-byte pieces of a pixel, up to 28 taps, 16-byte aligned input; everything else (wider groups,
-    // unequal channel counts, odd channel counts, any alignment) goes to the direct kernel
+    // unequal channel counts, odd channel counts, any alignment) is shared out in run()
     const bool narrow = sh->Cin == sh->Cout && (gs == 1 || gs == 2 || gs == 4) && sh->Cin % 16 == 0 &&
                         sh->KH * sh->KW <= 28 && aligned16(d_x);
     const int64_t Ho = (sh->H + 2 * sh->pad - sh->KH) / sh->stride + 1;

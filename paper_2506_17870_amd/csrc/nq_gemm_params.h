@@ -104,8 +104,8 @@ struct GroupGeom {
     int hin, hout;    // (its whole groups); 0 otherwise
 };
 
-// Geometry of the stationary-weights GEMM (1x1 convolutions with 64, 128 or 256 input channels at any stride,
-// GEMMs with that K): persistent blocks, each a column group of 64 * wn columns and a slot of row tiles.
+// Geometry of the stationary-weights GEMM (1x1 convolutions with up to 256 input channels, a multiple of 16, at any
+// stride, GEMMs with that K): persistent blocks, each a column group of 64 * wn columns and a slot of row tiles.
 struct StatGeom {
     int ks;            // K steps of 64: 1, 2 or 4
     int wn;            // waves along N: 4, 2 or 1 (256, 128 or 64 columns per block)
@@ -198,7 +198,7 @@ template <int H, int L>
 void launch_nested_gemm_big(bool full, const GemmParams &p, int tm_forced, int *tm_used, hipStream_t st,
                             void *ev_start, void *ev_stop);
 
-// Short reductions (K = 64, 128, 256): weights stationary in registers, persistent blocks over row tiles.
+// Short reductions (K up to 256): weights stationary in registers, persistent blocks over row tiles.
 template <int H, int L>
 void launch_nested_gemm_stat(bool full, const GemmParams &p, const StatGeom &g, hipStream_t st, void *ev_start,
                              void *ev_stop);

@@ -158,7 +158,7 @@ __global__ void __launch_bounds__(64 * NWS, 2) k_nested_gemm_slab(const GemmPara
     epi_tile<EPI>(p, acc, SHIFT, e, m0, rows, nb * 32, lane, res);
 }
 
-// Defined here, instantiated once per (h, l) by nq_gemm_inst.hip.  The caller has checked the shape (slab_ok in
+// Defined here, instantiated once per (h, l) by nq_gemm_slab.hip.  The caller has checked the shape (slab_ok in
 // nq_gemm.hip) and that the problem takes a vector epilogue.
 template <int H, int L>
 void launch_nested_gemm_slab(bool full, const GemmParams &p, int x_bytes, hipStream_t st, void *ev_start, void *ev_stop)
