@@ -44,17 +44,22 @@ RIDGE = MFMA_INT8_PEAK_TOPS * 1e12 / (HBM_PEAK_GBS * 1e9)   # op per byte above 
 TRAFFIC = {   # profiles/gemm_big_conv3x3_b128_counters.txt: FETCH_SIZE x 1.999 KiB, WRITE_SIZE x 1.000 KiB, means per dispatch
     "k_nested_gemm_big<6,2,full,int8 out,TM=6,filter>": dict(sources="30a3552ef1432191", fetch_bytes=14219319, write_bytes=6422528),
     "k_nested_gemm_big<6,2,part,int8 out,TM=6,filter>": dict(sources="30a3552ef1432191", fetch_bytes=13005871, write_bytes=6422528),
+    "k_nested_gemm_stat<6,2,full,int8 out,K=256,WN=4>": dict(sources="9afa8e74eec63080", fetch_bytes=34245294, write_bytes=26970317),
+    "k_nested_gemm_stat<6,2,part,int8 out,K=256,WN=4>": dict(sources="9afa8e74eec63080", fetch_bytes=33739487, write_bytes=27042918),
 }
-KERNEL_SOURCES = ("nq_gemm_big.h", "nq_epilogue.h", "nq_codec.h", "nq_gemm_kernel.h")   # what k_nested_gemm_big is made of
+KERNEL_SOURCES = {   # what a kernel is made of
+    "k_nested_gemm_big": ("nq_gemm_big.h", "nq_epilogue.h", "nq_codec.h", "nq_gemm_kernel.h"),
+    "k_nested_gemm_stat": ("nq_gemm_stat.h", "nq_epilogue.h", "nq_codec.h", "nq_gemm_kernel.h"),
+}
 FAMILY = {1: "k_nested_gemm", 2: "k_nested_conv_window", 3: "k_nested_conv_rowstream", 4: "k_nested_gemm_big",
           5: "k_nested_conv_smallcin", 6: "k_nested_gemm_skinny", 7: "k_nested_conv_grouped", 8: "k_nested_gemm_words", 9: "k_nested_gemm_stat",
           10: "k_nested_conv_grouped_mid / _any", 11: "k_nested_gemm_slab"}
 
 
-def kernel_sources_digest():
+def kernel_sources_digest(kernel):
     import hashlib
     h = hashlib.sha256()
-    for name in KERNEL_SOURCES:
+    for name in KERNEL_SOURCES[kernel]:
         with open(os.path.join(ROOT, "paper_2506_17870_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()[:16]
@@ -277,7 +282,7 @@ def main():
         achieved, peak, unit = bytes_launch / avg_us / 1e3, HBM_PEAK_GBS, "GB/s"
     traffic = None
     t = TRAFFIC.get(inst)
-    if t and t["sources"] == kernel_sources_digest():
+    if t and t["sources"] == kernel_sources_digest(inst.split("<")[0]):
         traffic = t["fetch_bytes"] + t["write_bytes"]
     roofline = dict(bound=bound, achieved=achieved, peak=peak, unit=unit, frac=achieved / peak, traffic=traffic,
                     kernel=inst, launches_per_step=g["n"] // 3, avg_kernel_us=avg_us,
