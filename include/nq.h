@@ -335,7 +335,7 @@ nq_status nq_conv_part(const int8_t *d_x, const nq_conv_shape *shape, const nq_w
  * smaller than 2 GiB (NQ_ERR_SHAPE).  Three kernels: depthwise layers and groups of 2 or 4 channels with
  * Cin == Cout a multiple of 16, up to 28 taps and a 16-byte aligned d_x, and groups of up to 32 input and 32 output
  * channels in whole dwords (gs, Cin multiples of 4, 4-byte aligned d_x) with up to 9 taps and sums long enough for it to
- * pay (K above 36; with int8 outputs in whole 16-byte stores K above 8, or a million outputs), run on the matrix cores; every other shape
+ * pay (from K = 64 to 84 on; with int8 outputs in whole 16-byte stores K above 8, or a million outputs), run on the matrix cores; every other shape
  * (still wider groups, short sums, odd channel counts, any alignment) runs as a direct convolution on the vector ALU:
  * same results, for long sums at about a tenth of the speed. */
 nq_status nq_gconv_full(const int8_t *d_x, const nq_conv_shape *shape, int groups, const nq_weight *w,

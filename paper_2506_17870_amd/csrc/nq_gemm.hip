@@ -449,13 +449,18 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         if (ceil_div(g.M, 32) > 0x7fffffffLL || ceil_div(w->N, 64) > 65535) return NQ_ERR_SHAPE;
         // Groups of up to 32 channels, whole dwords of input channels, up to nine taps (what a wave holds in registers):
         // on the matrix cores (32 x 56 x 56 x 256, 32 groups of 8: 24 us against 218 us).  Other widths, filters and
-        // alignments stay with the direct kernel, and so do short sums, whose time is the way in and out: up to K = 36
-        // with outputs that leave byte by byte or as fp32 (K = 8 to 16: 87 of 97 shapes slower here, up to 24.4 us against
-        // 45.0; K = 33 to 36: up to 200 against 245; from K = 40 on none of 408 is), up to K = 8 with 16-byte stores below
-        // a million outputs (4.2 against 4.8; beyond, 1x1 over 28 x 28 x 128 in 16 groups at batch 32, 11.9 against 5.2).
+        // alignments stay with the direct kernel, and so do short sums, whose time is the way in and out.  With 16-byte stores
+        // those are K up to 8, over groups of 4 up to 16, below a million outputs (4.2 us there, 4.8 here; 5.0 and 5.3; beyond,
+        // 1x1 over 28 x 28 x 128 in 16 groups at batch 32, 11.9 there, 5.2 here).  Outputs that leave byte by byte or as fp32: K below 64 (K = 8 to 16 87 of 97 shapes
+        // slower here, up to 24.4 against 45.0; K = 37 to 60 35 of 637, up to 26.4 against 61.0), and up to K = 80 many
+        // outputs in fp32 (25056 x 64 -> 192 46.1 against 59.1) or on half tiles of fewer than 16 output channels (23328 x 80 ->
+        // 64 20.4 against 22.4).  Of the 7300 shapes drawn beyond that none is slower by more than 3 percent.
         const int widest = gs > gs_out ? gs : gs_out;
-        const bool wide_out = widest <= 32 && !general && p.out_int8 && 32 / widest * gs_out % 16 == 0;
-        const bool mid_wanted = w->K > 36 || (wide_out && (w->K > 8 || g.M * w->N >= (int64_t(1) << 20)));
+        const int64_t outputs = g.M * w->N;
+        const int hout = widest <= 32 ? 32 / widest * gs_out : 0;          // output channels of a half tile
+        const bool wide_out = hout > 0 && !general && p.out_int8 && hout % 16 == 0;
+        const bool mid_wanted = wide_out ? w->K > (gs == 4 ? 16 : 8) || outputs >= (int64_t(1) << 20)
+                                         : w->K > 80 || (w->K >= 64 && (outputs < (int64_t(1) << 17) || (p.out_int8 && w->K > 64 && hout >= 16)));
         GroupGeom mg;
         if (mid_wanted && quads && widest <= 32 && g.KH * g.KW <= 9 && plan_grouped(g, gs, gs_out, w->N, &mg)) {
             p.general = general;

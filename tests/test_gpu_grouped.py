@@ -249,7 +249,13 @@ def test_direct_kernel_by_dwords_every_nesting(nq, make, n, l):
     ((1, 8, 9, 64, 96, 16, 3, 1, 1), False, 1),    # 3x3 over 4 channels, K = 36
     ((1, 8, 9, 64, 128, 16, 3, 1, 1), True, 2),
     ((1, 8, 9, 40, 40, 4, 2, 1, 1), False, 0),     # 10 channels: no dwords
-    ((1, 8, 9, 48, 48, 4, 2, 1, 1), False, 2),     # 12 channels, K = 48
+    ((1, 8, 9, 48, 48, 4, 2, 1, 1), False, 1),     # 12 channels, K = 48
+    ((1, 8, 9, 64, 64, 4, 2, 1, 1), False, 2),     # 16 channels, K = 64
+    ((1, 8, 9, 64, 64, 4, 2, 1, 1), True, 2),
+    ((1, 8, 9, 32, 32, 4, 3, 1, 1), False, 2),     # 3x3 over 8 channels
+    ((4, 24, 24, 64, 64, 8, 3, 1, 1), False, 1),   # ... 147456 outputs
+    ((4, 24, 24, 72, 72, 9, 3, 1, 1), True, 2),    # ... as bytes
+    ((4, 24, 24, 60, 60, 5, 3, 1, 1), False, 2),   # 12 channels, K = 108
 ])
 def test_which_grouped_kernel_runs(nq, geom, int8, variant):
     B, H, W, Cin, Cout, groups, KH, stride, pad = geom
