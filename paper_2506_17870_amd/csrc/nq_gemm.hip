@@ -531,6 +531,12 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
             if (w->K < 640 || !(filled || (w->K >= 768 && ceil_div(g.M, 128) * col_tiles <= 192))) big_wanted = false;
             if (plan_window(g, d_x, &wg0, &lds0) && (wg0.CK > 64 || w->K < 2304)) big_wanted = false;
         }
+        // Short reductions over such channel counts stay with the generic kernel where its 128 x 256 tiles fill the units
+        // once (12032 x 320 -> 336 10.6 us there, 12.1 here; with half or twice as many tiles 0.7 to 0.98 times the time here).
+        if (conv_gemm && !cin_pow2 && w->K < 400) {
+            const int64_t tiles = ceil_div(g.M, 128) * ceil_div(w->N, 256);
+            if (tiles > 128 && tiles <= 256) big_wanted = false;
+        }
     }
     // Outputs too small to fill the chip with large tiles: 32 x 32 blocks that split K over their waves.  Up to one block
     // per compute unit they are ahead of every other kernel (197 x 3072 -> 768: 7.7 us against 16.7 us for the large one;

@@ -185,6 +185,21 @@ def test_large_kernel_with_ragged_outputs(nq, M, N, K, family):
     check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, True)
 
 
+@pytest.mark.parametrize("M,N,K,family", [(8192, 400, 320, 4), (8320, 400, 320, 1), (16384, 400, 320, 1), (16512, 400, 320, 4),
+                                          (8320, 400, 400, 4)])
+def test_large_kernel_on_short_reductions(nq, M, N, K, family):
+    # the generic kernel keeps what fills the units once with its 128 x 256 tiles
+    case = make_case(nq, N, K, 8, 2, seed=K)
+    x = inputs.uniform_activations((M, K), seed=M)
+    epi, _, okw = epi_pair(nq, case, True, (M,), dump=False, s_a=0.02, out_int8=True, inv_s_out=4.0)
+    y = torch.full((M, N), 77, dtype=torch.int8, device="cuda")
+    nq.nq_gemm_full(dev(x), M, case.W.desc, epi, y)
+    torch.cuda.synchronize()
+    assert nq.nq_profile_last_kernel()[0] == family
+    acc = oracle.gemm_acc(x, case.ow_full)
+    check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, True)
+
+
 @pytest.mark.parametrize("Cin,family", [(192, 2), (320, 4), (384, 2), (448, 4), (176, 4)])
 def test_large_kernel_or_windows_with_ragged_outputs(nq, Cin, family):
     x = inputs.uniform_activations((1, 12, 13, Cin), seed=Cin)
