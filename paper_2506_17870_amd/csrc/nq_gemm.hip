@@ -555,7 +555,10 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     const bool skinny_ok = g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0 && g.M <= 64 && w->K % 16 == 0 &&
                            aligned16(d_x) && ceil_div(w->N, 32) <= 0x7fffffffLL;
     const int64_t slab_blocks = ceil_div(g.M, 32) * ceil_div(w->N, 32);
-    const bool slab_wanted = (slab_blocks <= 256 || (slab_blocks <= 512 && (w->K <= 512 || w->K >= 2048))) &&
+    // The stationary kernel's 128-column blocks with fp32 outputs are the exception at K = 128 (5054 x 128 -> 65 4.8 us
+    // there, 6.0 here, 216 shapes of 257 to 512 blocks 0.9 to 1.23 times the time): one block per unit there as well.
+    const bool stat_columns = w->K == 128 && w->N > 64 && w->N <= 128 && !p.out_int8;
+    const bool slab_wanted = (slab_blocks <= 256 || (slab_blocks <= 512 && !stat_columns && (w->K <= 512 || w->K >= 2048))) &&
                              w->K > 64 &&
                              !(skinny_ok && w->K >= 256 && (g.M <= 32 || slab_blocks > 256 || (p.KB >= 12 && p.KB <= 16)));
     auto run_slab = [&]() {

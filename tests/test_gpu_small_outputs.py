@@ -108,6 +108,8 @@ def test_small_outputs_by_the_library(nq):
     (8192, 64, 48, True, 11), (8224, 64, 48, True, 1), (3136, 256, 32, False, 1), (16384, 32, 96, False, 11),
     (12256, 64, 144, True, 11), (12320, 64, 144, True, 1), (29008, 32, 192, True, 1), (20480, 64, 520, False, 11),
     (20512, 64, 520, False, 1), (32768, 64, 776, True, 11), (32800, 64, 776, True, 1),
+    # fp32 columns of one 128-wide block of the stationary kernel: one block per unit
+    (2048, 128, 128, False, 11), (2080, 128, 128, False, 9), (2080, 128, 128, True, 11), (2080, 132, 128, False, 11),
     # up to 64 rows: the kernel for few rows where its split has the fewer idle rounds
     (33, 256, 704, False, 11), (33, 256, 720, False, 6), (64, 96, 1024, True, 6), (40, 96, 1040, False, 11), (32, 96, 512, False, 6)])
 def test_small_outputs_where_they_are_the_faster_kernel(nq, M, N, K, i8, family):
