@@ -629,9 +629,10 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     // What is left would go to the generic kernel, which walks K one step at a time: small blocks again, up to the number
     // at which both take as long.  Both sides measured on N = 16 to 1000, time against the generic kernel's, worst of
     // them at the limit and at the next number up: K = 16 to 96 0.9 to 1.0 at 512 blocks, 1.3 at 640; K = 144 to 256 0.93
-    // at 768, 1.2 at 900; K = 328 to 640 0.90 at 1280, 1.17 at 1600; K = 776 to 2008 0.95 at 2048, 1.2 at 2500.  (A single K
-    // step leaves three of four waves without work, and up to 512 blocks that costs nothing: the launch is what takes 4 us.)
-    const int64_t slab_limit = w->K <= 128 ? 512 : (w->K < 320 ? 768 : (w->K < 768 ? 1280 : 2048));
+    // at 768, 1.2 at 900; K = 272 to 320 0.92 at 1024, 1.05 at 1150; K = 352 to 720 0.92 at 1280, 1.15 at 1450; K = 776 to 2008
+    // 0.95 at 2048, 1.2 at 2500.  (A single K step leaves three of four waves without work, and up to 512 blocks that costs
+    // nothing: the launch is what takes 4 us.)
+    const int64_t slab_limit = w->K <= 128 ? 512 : w->K <= 256 ? 768 : w->K < 352 ? 1024 : w->K < 768 ? 1280 : 2048;
     if (slab_fits && force == 0 && slab_blocks <= slab_limit) return run_slab();
     const int tile = pick_tile(g.M, w->N);
     if (ceil_div(g.M, NQ_TILE_BM[tile]) > 0x7fffffffLL || ceil_div(w->N, NQ_TILE_BN[tile]) > 65535)

@@ -106,7 +106,8 @@ def test_small_outputs_by_the_library(nq):
 @pytest.mark.parametrize("M,N,K,i8,family", [
     # what no other kernel wants: small blocks up to the number at which the generic kernel takes as long, per length of K
     (8192, 64, 48, True, 11), (8224, 64, 48, True, 1), (3136, 256, 32, False, 1), (16384, 32, 96, False, 11),
-    (12256, 64, 144, True, 11), (12320, 64, 144, True, 1), (29008, 32, 192, True, 1), (20480, 64, 520, False, 11),
+    (12256, 64, 144, True, 11), (12320, 64, 144, True, 1), (29008, 32, 192, True, 1),
+    (16384, 64, 320, True, 11), (16416, 64, 320, False, 1), (20480, 64, 520, False, 11),
     (20512, 64, 520, False, 1), (32768, 64, 776, True, 11), (32800, 64, 776, True, 1),
     # fp32 columns of one 128-wide block of the stationary kernel: one block per unit
     (2048, 128, 128, False, 11), (2080, 128, 128, False, 9), (2080, 128, 128, True, 11), (2080, 132, 128, False, 11),
