@@ -125,6 +125,19 @@ def test_small_outputs_where_they_are_the_faster_kernel(nq, M, N, K, i8, family)
     check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, i8)
 
 
+@pytest.mark.parametrize("B,H,N,int8,family", [(1, 8, 460, False, 3), (1, 16, 96, False, 3), (1, 8, 96, True, 11), (1, 17, 96, False, 11)])
+def test_small_outputs_or_stationary_rows(nq, B, H, N, int8, family):
+    x = inputs.uniform_activations((B, H, H, 64), seed=N)
+    case = make_case(nq, N, 576, 8, 2, seed=H)
+    epi, _, okw = epi_pair(nq, case, True, (B, H, H), dump=False, s_a=0.02, out_int8=int8, inv_s_out=4.0)
+    y = torch.full((B, H, H, N), 77, dtype=torch.int8 if int8 else torch.float32, device="cuda")
+    nq.nq_conv_full(dev(x), nq.nq_conv_shape(B, H, H, 64, N, 3, 3, 1, 1), case.W.desc, epi, y)
+    torch.cuda.synchronize()
+    assert nq.nq_profile_last_kernel()[0] == family
+    acc = oracle.conv_acc(x, case.ow_full.reshape(N, 3, 3, 64), 1, 1)
+    check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, int8)
+
+
 # ---- short reductions in steps of 16, activations in steps of 8 ------------------------------------------------
 @pytest.mark.parametrize("M,N,K", [(100, 64, 16), (333, 96, 32), (333, 144, 48), (4097, 192, 96), (129, 272, 144),
                                    (700, 64, 192), (257, 40, 240)])
