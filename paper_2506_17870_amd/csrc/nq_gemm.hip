@@ -521,16 +521,16 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
             big_wanted = false;
         // With the element-wise epilogue (ragged N and the like) the large kernel runs one block per unit, and over channel
         // counts that are no power of two it is ahead of the generic kernel from K = 640 on (15000 rows, 250 columns: K = 272
-        // 42.1 us there and 45.6 here, K = 720 51.9 and 48.0), with several column tiles if they are filled (15000 x 720 ->
-        // 530 81.5 there and 98.6 here) or the blocks few and K at least 1024 (8179 x 800 -> 305 26.6 and 28.4); and of the
-        // windowed kernel in chunks of 64 channels from K = 2304 on (3x3 at up to 6272 pixels: over 192 channels 0.8 to 1.2
-        // times the windowed kernel's time, over 320 and 448 channels 0.6 to 1.03), in chunks of 128 not safely (over 384 0.7
-        // to 1.1).
+        // 42.1 us there and 45.6 here, K = 720 51.9 and 48.0), with several column tiles if they are nine tenths filled (15000 x
+        // 720 -> 530 81.5 there and 98.6 here; 5417 x 1152 -> 1340 52.6 and 58.2) or the blocks few and K at least 1024 (8179 x
+        // 800 -> 305 26.6 and 28.4); and of the windowed kernel in chunks of 64 channels from K = 2304 on up to 4096 pixels
+        // (3x3 over 192 channels 0.8 to 1.2 times the windowed kernel's time, over 320 and 448 channels 0.6 to 1.03; 36000 pixels,
+        // 320 -> 116 58.9 there and 79.6 here), in chunks of 128 not safely (over 384 0.7 to 1.1).
         if (conv_gemm && !cin_pow2 && p.general) {
             const int64_t col_tiles = ceil_div(w->N, 256);
-            const bool filled = col_tiles == 1 || w->N * 20 >= col_tiles * 256 * 17;
-            if (w->K < 640 || !(filled || (w->K >= 1024 && ceil_div(g.M, 128) * col_tiles <= 192))) big_wanted = false;
-            if (plan_window(g, d_x, &wg0, &lds0) && (wg0.CK > 64 || w->K < 2304)) big_wanted = false;
+            const bool filled = col_tiles == 1 || w->N * 10 >= col_tiles * 256 * 9;
+            if (w->K < 640 || !(filled || (w->K >= 1024 && ceil_div(g.M, 128) * col_tiles <= 128))) big_wanted = false;
+            if (plan_window(g, d_x, &wg0, &lds0) && (wg0.CK > 64 || w->K < 2304 || g.M > 4096)) big_wanted = false;
         }
         // Short reductions over such channel counts stay with the generic kernel where its 128 x 256 tiles fill the units
         // once (12032 x 320 -> 336 10.6 us there, 12.1 here; with half or twice as many tiles 0.7 to 0.98 times the time here).

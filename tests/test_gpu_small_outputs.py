@@ -186,7 +186,7 @@ def test_large_kernel_any_multiple_of_sixteen(nq, choice):
 
 
 @pytest.mark.parametrize("M,N,K,family", [
-    (300, 130, 624, 1), (300, 130, 656, 4), (200, 258, 1008, 1), (200, 258, 1040, 4), (12416, 258, 1040, 1), (300, 500, 656, 4),
+    (300, 130, 624, 1), (300, 130, 656, 4), (200, 258, 1008, 1), (200, 258, 1040, 4), (12416, 258, 1040, 1), (300, 500, 656, 4), (300, 450, 656, 1), (300, 470, 656, 4),
     (300, 130, 1024, 4)])
 def test_large_kernel_with_ragged_outputs(nq, M, N, K, family):
     # the element-wise epilogue: long reductions, filled column tiles or few blocks; K = 1024 is the plain form
