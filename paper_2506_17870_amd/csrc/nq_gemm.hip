@@ -558,14 +558,16 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     // The stationary kernel's 128-column blocks with fp32 outputs are the exception at K = 128 (5054 x 128 -> 65 4.8 us
     // there, 6.0 here, 216 shapes of 257 to 512 blocks 0.9 to 1.23 times the time): one block per unit there as well.
     const bool stat_columns = w->K == 128 && w->N > 64 && w->N <= 128 && !p.out_int8;
-    // 3x3 over 64 channels, fp32 outputs of up to 256 pixels: the register-stationary kernel, for weights that no cache holds
-    // (8 x 8 x 64 -> 460 4.2 us there, 4.8 here; with 257 pixels and more 0.8 to 0.95 times its time here; warm both 4.1).
+    // Filters the register-stationary kernel takes (3x3 over 64 channels, 2x2 over 64 and 128) stay there above one small block
+    // per unit (2x2 over 128 channels, 257 to 512 blocks: 4.4 us there, 5.0 here; 143 of 146 shapes slower here), and from
+    // K = 512 on up to 256 pixels, where it meets cold weights faster (8 x 8 x 64 -> 460 4.2 us there, 4.8 here; with 257
+    // pixels and more 0.8 to 0.95 times its time here; warm both 4.1).
     StreamGeom few;
     int few_blocks = 0;
-    const bool few_pixels = !p.out_int8 && g.M <= 256 && g.Cin == 64 && g.KH * g.KW == 9 &&
-                            plan_rowstream(g, d_x, w->N, &few, &few_blocks);
-    const bool slab_wanted = (slab_blocks <= 256 || (slab_blocks <= 512 && !stat_columns && (w->K <= 512 || w->K >= 2048))) &&
-                             w->K > 64 && !few_pixels &&
+    const bool streamed = g.KH * g.KW > 1 && plan_rowstream(g, d_x, w->N, &few, &few_blocks);
+    const bool slab_wanted = (slab_blocks <= 256 || (slab_blocks <= 512 && !stat_columns && !streamed &&
+                                                     (w->K <= 512 || w->K >= 2048))) &&
+                             w->K > 64 && !(streamed && w->K >= 512 && g.M <= 256) &&
                              !(skinny_ok && w->K >= 256 && (g.M <= 32 || slab_blocks > 256 || (p.KB >= 12 && p.KB <= 16)));
     auto run_slab = [&]() {
         if (!commit()) return NQ_ERR_HIP;

@@ -125,16 +125,21 @@ def test_small_outputs_where_they_are_the_faster_kernel(nq, M, N, K, i8, family)
     check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, i8)
 
 
-@pytest.mark.parametrize("B,H,N,int8,family", [(1, 8, 460, False, 3), (1, 16, 96, False, 3), (1, 8, 96, True, 11), (1, 17, 96, False, 11)])
-def test_small_outputs_or_stationary_rows(nq, B, H, N, int8, family):
-    x = inputs.uniform_activations((B, H, H, 64), seed=N)
-    case = make_case(nq, N, 576, 8, 2, seed=H)
-    epi, _, okw = epi_pair(nq, case, True, (B, H, H), dump=False, s_a=0.02, out_int8=int8, inv_s_out=4.0)
-    y = torch.full((B, H, H, N), 77, dtype=torch.int8 if int8 else torch.float32, device="cuda")
-    nq.nq_conv_full(dev(x), nq.nq_conv_shape(B, H, H, 64, N, 3, 3, 1, 1), case.W.desc, epi, y)
+@pytest.mark.parametrize("B,H,Cin,k,N,int8,family", [
+    (1, 8, 64, 3, 460, False, 3), (1, 16, 64, 3, 96, True, 3), (1, 17, 64, 3, 96, False, 11),     # few pixels
+    (1, 8, 64, 2, 96, False, 11), (1, 18, 128, 2, 96, True, 11), (1, 17, 128, 2, 32, True, 3),    # 17 x 17 and 16 x 16 outputs
+    (4, 33, 128, 2, 64, True, 11), (5, 33, 128, 2, 64, True, 3), (5, 33, 64, 2, 64, False, 3)])   # one block per unit
+def test_small_outputs_or_stationary_rows(nq, B, H, Cin, k, N, int8, family):
+    pad = k // 2 if k == 3 else 0
+    ho = H + 2 * pad - k + 1
+    x = inputs.uniform_activations((B, H, H, Cin), seed=N)
+    case = make_case(nq, N, k * k * Cin, 8, 2, seed=H)
+    epi, _, okw = epi_pair(nq, case, True, (B, ho, ho), dump=False, s_a=0.02, out_int8=int8, inv_s_out=4.0)
+    y = torch.full((B, ho, ho, N), 77, dtype=torch.int8 if int8 else torch.float32, device="cuda")
+    nq.nq_conv_full(dev(x), nq.nq_conv_shape(B, H, H, Cin, N, k, k, 1, pad), case.W.desc, epi, y)
     torch.cuda.synchronize()
     assert nq.nq_profile_last_kernel()[0] == family
-    acc = oracle.conv_acc(x, case.ow_full.reshape(N, 3, 3, 64), 1, 1)
+    acc = oracle.conv_acc(x, case.ow_full.reshape(N, k, k, Cin), 1, pad)
     check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, int8)
 
 
