@@ -29,10 +29,12 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
 def _units():
     units = [(os.path.join(CSRC, f + ".hip"), os.path.join(OBJ, f + ".o"), [])
              for f in ("nq_pack", "nq_page", "nq_glue", "nq_gemm", "nq_gemm_words")]   # nq_yardsticks.hip is a program of its own
-    for h, l in NESTINGS:
-        for part in (1, 0, 2, 3):
+    # the longest first (the large kernel's units take twice as long as the next), so that none is left to run alone at the end
+    for part in (1, 0, 3, 2):
+        for h, l in NESTINGS:
             units.append((os.path.join(CSRC, "nq_gemm_inst.hip"), os.path.join(OBJ, f"nq_gemm_inst_{h}{l}_{part}.o"),
                           [f"-DNQ_INST_H={h}", f"-DNQ_INST_L={l}", f"-DNQ_INST_PART={part}"]))
+    for h, l in NESTINGS:
         units.append((os.path.join(CSRC, "nq_gemm_slab.hip"), os.path.join(OBJ, f"nq_gemm_slab_{h}{l}.o"),
                       [f"-DNQ_INST_H={h}", f"-DNQ_INST_L={l}"]))
     return units
