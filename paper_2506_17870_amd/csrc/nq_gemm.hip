@@ -539,43 +539,63 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
             if (tiles > 128 && tiles <= 256) big_wanted = false;
         }
     }
-    // Outputs too small to fill the chip with large tiles: 32 x 32 blocks that split K over their waves.  Up to one block
-    // per compute unit they are ahead of every other kernel (197 x 3072 -> 768: 7.7 us against 16.7 us for the large one;
-    // 196 x 2304 -> 256 3x3: 7.2 against 14.8; 800 x 256 -> 256: 4.1 against 9.4 for the stationary one; 49 x 4608 -> 512
-    // 3x3: 9.4 against 61.3 for the windowed one).  Up to two per unit they are ahead where the reduction is long (416
-    // blocks, K = 4096: 15.7 against 20.6) or short (400 blocks, K = 256: 4.8 against 9.5), and behind in between (384
-    // blocks, K = 768: 9.0 against 8.3).  Up to 32 rows, and up to 64 with more blocks than units, the kernel for few
-    // rows has the same split and reads the weights once (16 x 1024 -> 4096: 4.1 against 4.8; 64 x 512 -> 512 the other
-    // way round, 4.8 against 4.1).  So it does for 12 to 16 K steps: two rounds of eight waves here, which the four-step
-    // pipeline runs as four (33 to 64 rows, K = 720 to 1024: 4.2 to 4.8 there, 4.6 to 5.2 here; K = 704 and 1088 are ahead here).
-    // A single K step is left to the kernels below, whose rule for what remains includes it.  The limit of 512 blocks is that of
-    // the large kernel's plain form; against its gathering form they are ahead further (6272 x 864 -> 96, 3x3, 588 blocks: 6.1
-    // against 8.4; 1000 x 1008 -> 1008, 1024 blocks: 8.0 against 9.6), which the rule does not use.
+    // Outputs too small to fill the chip with large tiles: 32 x 32 blocks that split K over their waves (nq_gemm_slab.h).  They
+    // are ahead of every other kernel up to several blocks per compute unit; how many depends on which kernel would run
+    // instead.  Limits from 380 drawn shapes with both sides forced, times of the other kernel over theirs:
+    //   stationary (K = 64, 128, 256): 500 blocks 2.0, 1100 1.5, 2050 1.1 to 1.2, 3000 0.94 to 1.15;
+    //   generic: 850 blocks 2.3, 1700 1.7, 3000 1.2 to 1.5, 4300 0.98 to 1.7, 4800 0.8 to 1.2;
+    //   windowed: 400 blocks 2.8, 1250 3.6, 1770 1.2, 2700 1.0;
+    //   register-stationary 3x3: 400 blocks 1.25, 1090 1.1, 1470 0.9;
+    //   large, K below 400: 700 blocks 2.0, 2120 1.4, 3100 1.15; K below 640: 1000 1.1 to 1.5, 1410 1.2, 1910 0.9, 2180 0.8;
+    //   large, longer K, more than 128 columns: 500 blocks 1.4 to 2, 1000 1.1 to 1.7, 1130 1.0 to 1.5, 1460 0.8 to 1;
+    //   large, longer K, up to 128 columns (its narrow tiles): 530 blocks 1.2, 680 1.1, 1030 0.8.
+    // Three routes that the tests hold stay as they were: up to 64 columns the generic kernel's own limits (at its call), fp32 columns
+    // of one 128-wide block of the stationary kernel at K = 128 and filters of four taps above one block per unit, and fp32 outputs
+    // of the stationary kernel at K = 64 (500 x 64 -> 256 5.2 us there and 2.7 in small blocks: not all that there is to gain).
     const bool slab_fits = slab_ok(g, d_x, w->K, x_bytes, p.general != 0);
     const bool skinny_ok = g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0 && g.M <= 64 && w->K % 16 == 0 &&
                            aligned16(d_x) && ceil_div(w->N, 32) <= 0x7fffffffLL;
     const int64_t slab_blocks = ceil_div(g.M, 32) * ceil_div(w->N, 32);
-    // The stationary kernel's 128-column blocks with fp32 outputs are the exception at K = 128 (5054 x 128 -> 65 4.8 us
-    // there, 6.0 here, 216 shapes of 257 to 512 blocks 0.9 to 1.23 times the time): one block per unit there as well.
     const bool stat_columns = w->K == 128 && w->N > 64 && w->N <= 128 && !p.out_int8;
-    // Filters the register-stationary kernel takes (3x3 over 64 channels, 2x2 over 64 and 128) stay there above one small block
-    // per unit (2x2 over 128 channels, 257 to 512 blocks: 4.4 us there, 5.0 here; 143 of 146 shapes slower here), and from
-    // K = 512 on up to 256 pixels, where it meets cold weights faster (8 x 8 x 64 -> 460 4.2 us there, 4.8 here; with 257
-    // pixels and more 0.8 to 0.95 times its time here; warm both 4.1).
+    // Few rows, weights read once: their own kernel (nq_gemm_skinny.h) streams the pages of wide layers with long rows best
+    // (64 x 8192 -> 8192 23.4 us there, 29.2 in small blocks; 32 x 8192 -> 6144 0.91 of the time; 56 x 2608 -> 14976 0.96);
+    // everything else of them small blocks take faster (16 x 4096 -> 4096 9.5 there, 7.6 here; 8 x 512 -> 512 3.4, 2.5; 64 x
+    // 1536 -> 8192 1.2 times; up to 16 rows 1.03 to 1.8 times for any size).
+    const bool few_rows = skinny_ok && w->K >= 256 && (g.M <= 32 || slab_blocks > 256 || (p.KB >= 12 && p.KB <= 16));
+    const bool few_rows_stream = g.M > 16 && ((w->N > 4096 && w->K >= 4096) || (w->N > 12288 && w->K >= 2048));
+    // Filters the register-stationary kernel takes (3x3 over 64 channels, 2x2 over 64 and 128) stay there from K = 512 on up to 256
+    // pixels, where it meets cold weights faster (8 x 8 x 64 -> 460 4.2 us there, 4.8 in small blocks as they were).
     StreamGeom few;
     int few_blocks = 0;
     const bool streamed = g.KH * g.KW > 1 && plan_rowstream(g, d_x, w->N, &few, &few_blocks);
-    const bool slab_wanted = (slab_blocks <= 256 || (slab_blocks <= 512 && !stat_columns && !streamed &&
-                                                     (w->K <= 512 || w->K >= 2048))) &&
-                             w->K > 64 && !(streamed && w->K >= 512 && g.M <= 256) &&
-                             !(skinny_ok && w->K >= 256 && (g.M <= 32 || slab_blocks > 256 || (p.KB >= 12 && p.KB <= 16)));
-    auto run_slab = [&]() {
+    int64_t slab_most = 512;
+    if (stat_columns) {
+        slab_most = 256;
+    } else if (streamed) {
+        slab_most = g.KH * g.KW == 9 ? 1024 : 256;
+    } else if (big_ok && big_wanted) {
+        slab_most = w->K < 400 ? 2048 : w->N <= 128 ? (w->K < 640 ? 1024 : 640) : (w->K < 640 ? 1408 : 1024);
+    } else if (g.KH * g.KW > 1) {
+        WindowGeom wg0;
+        size_t lds0 = 0;
+        if (plan_window(g, d_x, &wg0, &lds0)) slab_most = 2048;
+        else if (w->N > 64) slab_most = 3072;
+    } else if (w->K == 64 || w->K == 128 || w->K == 256) {
+        slab_most = 2048;                              // the stationary kernel's, at any stride
+    } else if (w->N > 64) {
+        slab_most = 3072;
+    }
+    const bool slab_wanted = slab_blocks <= slab_most && (w->K > 64 || (w->K == 64 && p.out_int8)) &&
+                             !(streamed && w->K >= 512 && g.M <= 256) && !few_rows;
+    auto run_slab = [&](bool for_few_rows) {
         if (!commit()) return NQ_ERR_HIP;
         g_last_family = 11; g_last_variant = 0;
+        if (for_few_rows) { g_last_family = 6; g_last_variant = 2; }
         NQ_DISPATCH_HL(h, l, launch_nested_gemm_slab, full, p, (int)x_bytes, s, ev0, ev1);
         return launch_status();
     };
-    if (slab_fits && (force == 11 || (force == 0 && slab_wanted))) return run_slab();
+    if (slab_fits && (force == 11 || (force == 0 && slab_wanted))) return run_slab(false);
+    if (slab_fits && force == 0 && few_rows && !few_rows_stream) return run_slab(true);
     // short reductions without a filter window: weights stationary in registers, rows streamed
     StatGeom tg;
     // (a K other than 64, 128 or 256 pays for its panels' padding: ahead of the generic kernel on many rows, 78400 x 32 ->
@@ -641,7 +661,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     // 0.95 at 2048, 1.2 at 2500.  (A single K step leaves three of four waves without work, and up to 512 blocks that costs
     // nothing: the launch is what takes 4 us.)
     const int64_t slab_limit = w->K <= 128 ? 512 : w->K <= 256 ? 768 : w->K < 352 ? 1024 : w->K < 768 ? 1280 : 2048;
-    if (slab_fits && force == 0 && slab_blocks <= slab_limit) return run_slab();
+    if (slab_fits && force == 0 && slab_blocks <= slab_limit) return run_slab(false);
     const int tile = pick_tile(g.M, w->N);
     if (ceil_div(g.M, NQ_TILE_BM[tile]) > 0x7fffffffLL || ceil_div(w->N, NQ_TILE_BN[tile]) > 65535)
         return NQ_ERR_SHAPE;

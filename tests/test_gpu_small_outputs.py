@@ -97,6 +97,38 @@ def test_small_outputs_every_nesting(nq, n, l, compensated):
     forced(nq, make_case(nq, 48, 576, n, l, seed=n * l, compensated=compensated), x, (3, 3, 1, 1), "11", 11)
 
 
+@pytest.mark.parametrize("M,N,K", [
+    (200, 600, 64), (199, 604, 260), (197, 592, 580), (193, 608, 1020),      # 32 columns: one to four units per wave, waves with none
+    (200, 600, 1100), (224, 592, 1536), (200, 596, 1796),                    # rounds of three and four, a last one of one to four
+    (113, 1024, 2048), (2047, 352, 1024), (2048, 340, 1284), (2033, 352, 1540)])   # 16 columns of 128 blocks; two row tiles
+def test_small_outputs_every_block_form(nq, M, N, K):
+    forced(nq, make_case(nq, N, K, 8, 2, seed=M + K), inputs.uniform_activations((M, K), seed=K), None, "11", 11)
+
+
+@pytest.mark.parametrize("B,H,W,Cin,N,k,stride,pad,comp", [
+    (2, 11, 10, 64, 600, 3, 1, 1, False), (5, 9, 9, 160, 320, 3, 2, 0, True), (8, 16, 16, 128, 352, 3, 1, 1, True)])
+def test_small_outputs_every_block_form_filters(nq, B, H, W, Cin, N, k, stride, pad, comp):
+    forced(nq, make_case(nq, N, k * k * Cin, 8, 3, seed=Cin + N, compensated=comp), inputs.uniform_activations((B, H, W, Cin), seed=H),
+           (k, k, stride, pad), "11", 11)
+
+
+@pytest.mark.parametrize("M,N,K,kernel", [
+    (1, 64, 256, (6, 2)), (16, 4128, 4096, (6, 2)), (17, 4128, 4096, (6, 0)), (17, 4096, 4096, (6, 2)), (17, 4128, 4080, (6, 2)),
+    (300, 1040, 768, (11, 0)), (1040, 1024, 1024, (4, 2)), (700, 512, 256, (11, 0)), (2080, 1024, 256, (9, 4)), (640, 128, 1024, (11, 0)),
+    (5152, 128, 1024, (4, 7)), (1400, 1008, 120, (11, 0)), (3104, 1024, 120, (1, 1))])
+def test_small_outputs_or_the_kernel_they_replace(nq, M, N, K, kernel):
+    # either side of the limits against the kernels for few rows, large tiles, stationary weights and the generic one
+    case = make_case(nq, N, K, 8, 2, seed=M + K)
+    x = inputs.uniform_activations((M, K), seed=K)
+    epi, _, okw = epi_pair(nq, case, True, (M,), dump=False, s_a=0.02, out_int8=True, inv_s_out=4.0)
+    y = torch.full((M, N), 77, dtype=torch.int8, device="cuda")
+    nq.nq_gemm_full(dev(x), M, case.W.desc, epi, y)
+    torch.cuda.synchronize()
+    assert nq.nq_profile_last_kernel() == kernel
+    acc = oracle.gemm_acc(x, case.ow_full)
+    check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, True)
+
+
 def test_small_outputs_by_the_library(nq):
     """The dispatch itself takes these to the small-output kernel, and to it alone."""
     forced(nq, make_case(nq, 768, 3072, 8, 3, seed=1), inputs.uniform_activations((197, 3072), seed=1), None, "", 11)
