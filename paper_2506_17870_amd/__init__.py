@@ -1,5 +1,5 @@
 """NestQuant nested-integer hot path for AMD MI355X (gfx950): hand-written HIP kernels
-behind a C ABI (include/nq.h) with a thin ctypes binding.  PyTorch is used only for device
+behind a C ABI (include/nq.h) with a thin binding.  PyTorch is used only for device
 memory and streams.
 
 The binding (and with it libnq.so) is loaded on first use of any attribute, so that
@@ -16,6 +16,8 @@ def __getattr__(name):
         return importlib.import_module(f"{__name__}.{name}")
     binding = importlib.import_module(f"{__name__}.binding")
     try:
-        return getattr(binding, name)
+        value = getattr(binding, name)
     except AttributeError:
         raise AttributeError(f"module {__name__!r} has no attribute {name!r}") from None
+    globals()[name] = value            # the next access does not come here (3.5 us, as much as a layer's whole call)
+    return value

@@ -1,10 +1,11 @@
-"""ctypes binding of libnq.so -- argument marshalling only.
+"""Binding of libnq.so (ctypes; the inference calls through the small extension _nqcall) -- argument marshalling only.
 
 Every function has the name and the argument order of its C entry point in
 include/nq.h; tensors are PyTorch tensors used purely as owners of device (or pinned
 host) memory, streams are `torch.cuda.Stream` objects or raw handles.  No step of the
-path is computed here.  Importing this module fails if the library has not been built:
-there is no fallback.
+path is computed here.  Importing this module fails if the library or the extension has not been
+built: there is no fallback.  The extension takes the plain calls (tensors, integers, None, descriptors of
+this module); it hands anything else back untouched, and the ctypes call then accepts or refuses it.
 """
 from __future__ import annotations
 
@@ -139,6 +140,17 @@ _current_raw_stream = torch._C._cuda_getCurrentRawStream if hasattr(torch._C, "_
     lambda device: torch.cuda.current_stream(device).cuda_stream)
 
 
+from . import _nqcall as _fast  # noqa: E402  (csrc/nq_call.cpp)
+
+_fast.setup(torch.Tensor, nq_weight, nq_epilogue, nq_conv_shape, nq_cfg,
+            getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device), _current_raw_stream,
+            *[ctypes.cast(getattr(_lib, n), ctypes.c_void_p).value
+              for n in ("nq_gemm_part", "nq_gemm_full", "nq_conv_part", "nq_conv_full", "nq_gconv_part", "nq_gconv_full",
+                        "nq_quantize_decompose_pack")])
+# a forked child has to go through torch's own initialisation (and its error) again
+os.register_at_fork(after_in_child=lambda: _fast.set_stream_ready(False))
+
+
 def _ptr(t):
     if t is None:
         return None
@@ -151,7 +163,9 @@ def _ptr(t):
 def _stream(s):
     if s is None:
         # the raw handle: building a torch.cuda.Stream around it costs more than the rest of a call's argument handling
-        return _current_raw_stream(torch.cuda.current_device())
+        device = torch.cuda.current_device()          # initialises the GPU; after that the extension asks by itself
+        _fast.set_stream_ready(True)
+        return _current_raw_stream(device)
     if isinstance(s, int):
         return s
     return s.cuda_stream
@@ -197,6 +211,9 @@ def nq_quantize_tensor(d_x, count, n_bits, d_codes, d_scale, stream=None):
 
 
 def nq_quantize_decompose_pack(d_w, N, K, cfg, d_scale, d_packed_high, d_packed_low, stream=None):
+    st = _fast.quantize_pack(d_w, N, K, cfg, d_scale, d_packed_high, d_packed_low, stream if stream is None else _stream(stream))
+    if st >= 0:
+        return _check(st, "nq_quantize_decompose_pack")
     _check(_lib.nq_quantize_decompose_pack(_ptr(d_w), N, K, ctypes.byref(cfg), _ptr(d_scale), _ptr(d_packed_high),
                                            _ptr(d_packed_low), _stream(stream)), "nq_quantize_decompose_pack")
 
@@ -236,8 +253,9 @@ def nq_page_in_low(w: nq_weight, copy_stream=None):
 
 
 def _wlist(ws):
-    arr = (_wp * len(ws))(*[ctypes.pointer(w) for w in ws])
-    return arr
+    if all(type(w) is nq_weight for w in ws):        # (a pointer object per weight: 35 us for a network's hundred)
+        return (_wp * len(ws)).from_buffer((ctypes.c_void_p * len(ws))(*[ctypes.addressof(w) for w in ws]))
+    return (_wp * len(ws))(*[ctypes.pointer(w) for w in ws])
 
 
 def nq_weight_init_group(ws):
@@ -259,11 +277,17 @@ def make_epilogue(act_scale=1.0, d_bias=None, d_residual=None, residual_scale=0.
 
 
 def nq_gemm_full(d_x, M, w: nq_weight, epi: nq_epilogue, d_y, stream=None):
+    st = _fast.gemm(1, d_x, M, w, epi, d_y, stream if stream is None else _stream(stream))
+    if st >= 0:
+        return _check(st, "nq_gemm_full")
     _check(_lib.nq_gemm_full(_ptr(d_x), M, ctypes.byref(w), ctypes.byref(epi), _ptr(d_y), _stream(stream)),
            "nq_gemm_full")
 
 
 def nq_gemm_part(d_x, M, w: nq_weight, epi: nq_epilogue, d_y, stream=None):
+    st = _fast.gemm(0, d_x, M, w, epi, d_y, stream if stream is None else _stream(stream))
+    if st >= 0:
+        return _check(st, "nq_gemm_part")
     _check(_lib.nq_gemm_part(_ptr(d_x), M, ctypes.byref(w), ctypes.byref(epi), _ptr(d_y), _stream(stream)),
            "nq_gemm_part")
 
@@ -291,23 +315,54 @@ def nq_gemm_batch_static(jobs, full_bit, stream=None):
 
 
 def nq_conv_full(d_x, shape: nq_conv_shape, w: nq_weight, epi: nq_epilogue, d_y, stream=None):
+    st = _fast.conv(1, d_x, shape, w, epi, d_y, stream if stream is None else _stream(stream))
+    if st >= 0:
+        return _check(st, "nq_conv_full")
     _check(_lib.nq_conv_full(_ptr(d_x), ctypes.byref(shape), ctypes.byref(w), ctypes.byref(epi), _ptr(d_y),
                              _stream(stream)), "nq_conv_full")
 
 
 def nq_conv_part(d_x, shape: nq_conv_shape, w: nq_weight, epi: nq_epilogue, d_y, stream=None):
+    st = _fast.conv(0, d_x, shape, w, epi, d_y, stream if stream is None else _stream(stream))
+    if st >= 0:
+        return _check(st, "nq_conv_part")
     _check(_lib.nq_conv_part(_ptr(d_x), ctypes.byref(shape), ctypes.byref(w), ctypes.byref(epi), _ptr(d_y),
                              _stream(stream)), "nq_conv_part")
 
 
 def nq_gconv_full(d_x, shape: nq_conv_shape, groups: int, w: nq_weight, epi: nq_epilogue, d_y, stream=None):
+    st = _fast.gconv(1, d_x, shape, groups, w, epi, d_y, stream if stream is None else _stream(stream))
+    if st >= 0:
+        return _check(st, "nq_gconv_full")
     _check(_lib.nq_gconv_full(_ptr(d_x), ctypes.byref(shape), groups, ctypes.byref(w), ctypes.byref(epi), _ptr(d_y),
                               _stream(stream)), "nq_gconv_full")
 
 
 def nq_gconv_part(d_x, shape: nq_conv_shape, groups: int, w: nq_weight, epi: nq_epilogue, d_y, stream=None):
+    st = _fast.gconv(0, d_x, shape, groups, w, epi, d_y, stream if stream is None else _stream(stream))
+    if st >= 0:
+        return _check(st, "nq_gconv_part")
     _check(_lib.nq_gconv_part(_ptr(d_x), ctypes.byref(shape), groups, ctypes.byref(w), ctypes.byref(epi), _ptr(d_y),
                               _stream(stream)), "nq_gconv_part")
+
+
+def run_layer(full, d_x, sizes, w: nq_weight, act_scale, d_bias, d_residual, residual_scale, relu, out_int8, inv_out_scale, d_y,
+              stream=None):
+    """nq_conv_full / nq_conv_part of a square filter, sizes = (B, H, W, Cin, Cout, k, stride, pad), or, with sizes an integer,
+    nq_gemm_full / nq_gemm_part over that many rows, from the values of the descriptors (a layer's two descriptor objects take
+    longer to make than its launch)."""
+    gemm = isinstance(sizes, int)
+    st = _fast.layer(full, d_x, sizes if gemm else 0, None if gemm else sizes, w, act_scale, d_bias, d_residual, residual_scale, relu,
+                     out_int8, inv_out_scale, d_y, stream if stream is None else _stream(stream))
+    if st >= 0:
+        if st:
+            _check(st, ("nq_gemm_" if gemm else "nq_conv_") + ("full" if full else "part"))
+        return
+    epi = make_epilogue(act_scale, d_bias, d_residual, residual_scale, relu, out_int8, inv_out_scale)
+    if gemm:
+        (nq_gemm_full if full else nq_gemm_part)(d_x, sizes, w, epi, d_y, stream)
+    else:
+        (nq_conv_full if full else nq_conv_part)(d_x, nq_conv_shape(*sizes[:6], *sizes[5:]), w, epi, d_y, stream)
 
 
 def nq_set_tuning(key: int, value: int):

@@ -12,11 +12,13 @@ import concurrent.futures
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnq.so")
+CALL = os.path.join(HERE, "_nqcall.so")            # the binding's per-call part, a host-only extension (csrc/nq_call.cpp)
 YARDSTICKS = os.path.join(HERE, "nq_yardsticks")   # standalone hardware yardsticks (csrc/nq_yardsticks.hip)
 
 # (h, l): INT(8|h) for l = 1..6 and INT(6|h) for l = 1..4
@@ -78,6 +80,13 @@ def build(force: bool = False, jobs: int | None = None) -> str:
     # a kernel template that the host pass fails to instantiate shows up only as an undefined symbol at load time
     import ctypes
     ctypes.CDLL(LIB, mode=os.RTLD_NOW)
+    csrc = os.path.join(CSRC, "nq_call.cpp")
+    header = os.path.join(os.path.dirname(HERE), "include", "nq.h")
+    if force or not os.path.exists(CALL) or os.path.getmtime(CALL) < max(os.path.getmtime(csrc), os.path.getmtime(header)):
+        r = subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-fvisibility=hidden", "-Wall",
+                            "-I" + sysconfig.get_paths()["include"], csrc, "-o", CALL], capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError("g++ failed for nq_call:\n" + r.stderr[-4000:])
     ysrc = os.path.join(CSRC, "nq_yardsticks.hip")
     if force or not os.path.exists(YARDSTICKS) or os.path.getmtime(YARDSTICKS) < os.path.getmtime(ysrc):
         r = subprocess.run(["hipcc", *[f for f in FLAGS if f != "-fPIC"], ysrc, "-o", YARDSTICKS],

@@ -162,6 +162,9 @@ class NestedCNN:
                 self.hw[op["dst"]] = (1, 1)
             else:
                 self.buf[op["dst"]] = torch.empty((B, op["cout"]), dtype=torch.float32, device="cuda")
+        # (B, H, W, Cin, Cout, k, stride, pad) of every convolution
+        self.sizes = [(B, *self.hw[op["src"]], op["cin"], op["cout"], op["k"], op["stride"], op["pad"]) if op["op"] == "conv" else None
+                      for op in self.ops]
         # ops that are a branch of the graph: convolutions whose output is used only as the residual of a later layer
         # (the projection shortcuts of the first block of every stage)
         used_as_residual = {op["residual"] for op in self.ops if op.get("residual") is not None}
@@ -180,7 +183,7 @@ class NestedCNN:
             self.allocate(B, H, W)
         d_step = torch.zeros(1, dtype=torch.float32, device="cuda")
         self.out_scale[0] = float(in_scale)
-        for op, L in zip(self.ops, self.layers):
+        for i, (op, L) in enumerate(zip(self.ops, self.layers)):
             if op["op"] == "conv":
                 src = x if op["src"] == 0 else self.buf[op["src"]]
                 hs, ws = self.hw[op["src"]]
@@ -198,30 +201,29 @@ class NestedCNN:
                 del yf
             elif op["op"] in ("maxpool", "avgpool"):
                 self.out_scale[op["dst"]] = self.out_scale[op["src"]]   # neither a maximum nor a mean exceeds the input range
-            self._run_op(op, L, x, B, True, None)
+            self._run_op(i, op, L, x, B, True, None)
         torch.cuda.synchronize()
 
-    def _run_op(self, op, L, x, B, full, stream):
-        src = x if op["src"] == 0 else self.buf[op["src"]]
-        hs, ws = self.hw[op["src"]]
-        s_in = self.out_scale[op["src"]]
-        y = self.buf[op["dst"]]
-        if op["op"] == "maxpool":
-            nq.nq_maxpool_i8(src, B, hs, ws, src.shape[3], op["k"], op["stride"], op["pad"], y, stream)
-        elif op["op"] == "avgpool":
-            nq.nq_avgpool_i8(src, B, hs * ws, src.shape[3], s_in, 1.0 / self.out_scale[op["dst"]], y, stream)
-        elif op["op"] == "fc":
-            Wt, bias = L
-            (nq.nq_gemm_full if full else nq.nq_gemm_part)(src.view(B, -1), B, Wt.desc, nq.make_epilogue(s_in, bias), y,
-                                                           stream)
-        else:
-            Wt, bias = L
-            shape = nq.nq_conv_shape(B, hs, ws, op["cin"], op["cout"], op["k"], op["k"], op["stride"], op["pad"])
+    def _run_op(self, i, op, L, x, B, full, stream):
+        sid, did = op["src"], op["dst"]
+        src = x if sid == 0 else self.buf[sid]
+        s_in = self.out_scale[sid]
+        y = self.buf[did]
+        if op["op"] == "conv":
             res, s_r = None, 0.0
-            if op["residual"] is not None:
-                res, s_r = self.buf[op["residual"]], self.out_scale[op["residual"]]
-            epi = nq.make_epilogue(s_in, bias, res, s_r, op["relu"], True, 1.0 / self.out_scale[op["dst"]])
-            (nq.nq_conv_full if full else nq.nq_conv_part)(src, shape, Wt.desc, epi, y, stream)
+            rid = op["residual"]
+            if rid is not None:
+                res, s_r = self.buf[rid], self.out_scale[rid]
+            nq.run_layer(full, src, self.sizes[i], L[0].desc, s_in, L[1], res, s_r, op["relu"], True, 1.0 / self.out_scale[did], y,
+                         stream)
+        elif op["op"] == "fc":
+            nq.run_layer(full, src.view(B, -1), B, L[0].desc, s_in, L[1], None, 0.0, False, False, 1.0, y, stream)
+        else:
+            hs, ws = self.hw[sid]
+            if op["op"] == "maxpool":
+                nq.nq_maxpool_i8(src, B, hs, ws, src.shape[3], op["k"], op["stride"], op["pad"], y, stream)
+            else:
+                nq.nq_avgpool_i8(src, B, hs * ws, src.shape[3], s_in, 1.0 / self.out_scale[did], y, stream)
 
     def forward(self, x, in_scale: float, full: bool, keep=None, stream=None, branch_stream=None):
         """x: int8 NHWC device tensor.  Returns the fp32 logits [B, classes] (a buffer of the model: the next
@@ -235,7 +237,7 @@ class NestedCNN:
             self.allocate(B, H, W)
         self.out_scale[0] = float(in_scale)
         logits = None
-        main = stream if stream is not None else torch.cuda.current_stream()
+        main = stream if stream is not None or branch_stream is None else torch.cuda.current_stream()
         joins = {}                                   # tensor id -> event its branch recorded
         for i, (op, L) in enumerate(zip(self.ops, self.layers)):
             on_branch = branch_stream is not None and i in self.branch_ops
@@ -243,13 +245,13 @@ class NestedCNN:
                 fork, join = self.branch_events[i]
                 fork.record(main)                    # the branch starts from what the main path has produced so far
                 branch_stream.wait_event(fork)
-                self._run_op(op, L, x, B, full, branch_stream)
+                self._run_op(i, op, L, x, B, full, branch_stream)
                 join.record(branch_stream)
                 joins[op["dst"]] = join
             else:
                 if op.get("residual") in joins:
                     main.wait_event(joins.pop(op["residual"]))
-                self._run_op(op, L, x, B, full, stream)
+                self._run_op(i, op, L, x, B, full, stream)
             if op["op"] == "fc":
                 logits = self.buf[op["dst"]]
             if keep is not None:
