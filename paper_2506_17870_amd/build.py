@@ -3,8 +3,8 @@
     python -m paper_2506_17870_amd.build [--force]
 
 Objects go to _build/ next to this file, the library to paper_2506_17870_amd/libnq.so.
-Five translation units per nesting (h, l) hold the GEMM/convolution kernels, so the
-units compile in parallel; the GEMM over the paper's word pages is one unit for all nestings.
+Six translation units per nesting (h, l) hold the GEMM/convolution kernels, so the
+units compile in parallel.
 """
 from __future__ import annotations
 
@@ -30,15 +30,16 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=o
 
 def _units():
     units = [(os.path.join(CSRC, f + ".hip"), os.path.join(OBJ, f + ".o"), [])
-             for f in ("nq_pack", "nq_page", "nq_glue", "nq_gemm", "nq_gemm_words")]   # nq_yardsticks.hip is a program of its own
+             for f in ("nq_pack", "nq_page", "nq_glue", "nq_gemm")]   # nq_yardsticks.hip is a program of its own
     # the longest first (the large kernel's units take twice as long as the next), so that none is left to run alone at the end
     for part in (1, 0, 3, 2):
         for h, l in NESTINGS:
             units.append((os.path.join(CSRC, "nq_gemm_inst.hip"), os.path.join(OBJ, f"nq_gemm_inst_{h}{l}_{part}.o"),
                           [f"-DNQ_INST_H={h}", f"-DNQ_INST_L={l}", f"-DNQ_INST_PART={part}"]))
-    for h, l in NESTINGS:
-        units.append((os.path.join(CSRC, "nq_gemm_slab.hip"), os.path.join(OBJ, f"nq_gemm_slab_{h}{l}.o"),
-                      [f"-DNQ_INST_H={h}", f"-DNQ_INST_L={l}"]))
+    for f in ("nq_gemm_words", "nq_gemm_slab"):
+        for h, l in NESTINGS:
+            units.append((os.path.join(CSRC, f + ".hip"), os.path.join(OBJ, f"{f}_{h}{l}.o"),
+                          [f"-DNQ_INST_H={h}", f"-DNQ_INST_L={l}"]))
     return units
 
 

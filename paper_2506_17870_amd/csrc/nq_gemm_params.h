@@ -204,8 +204,9 @@ void launch_nested_gemm_stat(bool full, const GemmParams &p, const StatGeom &g, 
                              void *ev_stop);
 
 // GEMM over the paper's word pages (64 / k fields per 64-bit word); WH, WL: words per row of the two pages.
-// Not a template: nq_gemm_words.hip holds every nesting.
-void launch_nested_gemm_words(bool full, int h, int l, const GemmParams &p, int WH, int WL, hipStream_t st,
-                              void *ev_start, void *ev_stop);
+// Instantiated once per (h, l) by nq_gemm_words.hip.
+template <int H, int L>
+void launch_nested_gemm_words(bool full, const GemmParams &p, int WH, int WL, hipStream_t st, void *ev_start,
+                              void *ev_stop);
 
 }  // namespace nq

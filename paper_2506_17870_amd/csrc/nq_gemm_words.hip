@@ -1,5 +1,5 @@
-// Instantiations and launcher of the GEMM over the paper's word pages (nq_gemm_words.h): one kernel per
-// field width of the higher-bit page in part-bit mode, one per nesting and lower-bit format in full-bit mode.
+// Launcher of the GEMM over the paper's word pages (nq_gemm_words.h); one translation unit per nesting (-DNQ_INST_H=<h>
+// -DNQ_INST_L=<l>).
 #include "nq_gemm_words.h"
 
 namespace nq {
@@ -15,58 +15,58 @@ static void words_grant_lds(K kernel, size_t lds)
     }
 }
 
+template <int HB, int LB, int MODE, int NW, int RT, int CS, bool CONV, int EPI>
+static void launch_words_as(const GemmParams &p, int WH, int WL, hipStream_t st, void *ev_start, void *ev_stop)
+{
+    auto k = k_nested_gemm_words<HB, LB, MODE, NW, RT, CS, CONV, EPI>;
+    constexpr size_t lds = words_lds_bytes<HB, MODE == 0 ? 0 : LB, NW, RT, CS>();
+    words_grant_lds(k, lds);
+    launch_timed(k, dim3((unsigned)p.NB, (unsigned)((p.M + 32 * RT - 1) / (32 * RT))), dim3(64 * NW), lds, st, ev_start, ev_stop, p,
+                 WH, WL);
+}
+
 template <int HB, int LB, int MODE>
 static void launch_words(const GemmParams &p, int WH, int WL, hipStream_t st, void *ev_start, void *ev_stop)
 {
-    // Four waves per block, two or more blocks per compute unit; where a layer with long rows has fewer blocks
-    // than that, eight waves per block share a page's steps.
-    const dim3 grid((unsigned)p.NB, (unsigned)((p.M + 31) / 32));
-    const bool wide = (int64_t)grid.x * grid.y < 512 && WH >= 128;
-    // a filter other than 1x1 stride 1 gathers its rows from the NHWC input (four waves only)
+    const int64_t blocks = (int64_t)p.NB * ((p.M + 31) / 32);
+    // Eight waves share a page's steps where there is at most a block per unit (16 x 8192 -> 8192 30.7 us, with four 42.5; 32 x
+    // 1574 -> 5510 9.9, 11.2; with 246 blocks and K = 570 5.4, 5.2; K = 300 5.7, 5.4; with 484 blocks 28.7, 26.3).
+    const bool wide = blocks <= 256 && p.K >= 400;
+    // Two row tiles share the decoding of both pages where that is the time and blocks are left (700 x 4000 -> 700 26.3 us, with
+    // one row tile 21.4; 186 x 5292 -> 4643 55.6, 49.8; the higher-bit page alone 276 x 2220 -> 3295 18.1, 21.6).
+    const bool tall = MODE != 0 && p.K >= 2000 && blocks >= 400;
+#define NQ_WD(NW, RT, CS)                                                                                     \
+    do {                                                                                                      \
+        if (epi_mode(p) == EPI_F32) launch_words_as<HB, LB, MODE, NW, RT, CS, false, EPI_F32>(p, WH, WL, st, ev_start, ev_stop); \
+        else launch_words_as<HB, LB, MODE, NW, RT, CS, false, EPI_ANY>(p, WH, WL, st, ev_start, ev_stop);     \
+    } while (0)
     const bool gather = p.KH != 1 || p.KW != 1 || p.stride != 1 || p.pad != 0;
-    if (gather) {
-        auto k = k_nested_gemm_words<HB, LB, MODE, 4, true>;
-        constexpr size_t lds = words_lds_bytes<HB, LB, 4>();
-        words_grant_lds(k, lds);
-        launch_timed(k, grid, dim3(256), lds, st, ev_start, ev_stop, p, WH, WL);
-    } else if (wide) {
-        auto k = k_nested_gemm_words<HB, LB, MODE, 8, false>;
-        constexpr size_t lds = words_lds_bytes<HB, LB, 8>();
-        words_grant_lds(k, lds);
-        launch_timed(k, grid, dim3(512), lds, st, ev_start, ev_stop, p, WH, WL);
-    } else {
-        auto k = k_nested_gemm_words<HB, LB, MODE, 4, false>;
-        constexpr size_t lds = words_lds_bytes<HB, LB, 4>();
-        words_grant_lds(k, lds);
-        launch_timed(k, grid, dim3(256), lds, st, ev_start, ev_stop, p, WH, WL);
+    if (!gather) {
+        if (wide) {
+            NQ_WD(8, 1, 4);
+            return;
+        }
+        if constexpr (MODE != 0) {
+            if (tall) {
+                NQ_WD(8, 2, 2);
+                return;
+            }
+        }
+        NQ_WD(4, 1, 4);
+        return;
     }
+    // a filter other than 1x1 stride 1 gathers its rows from the NHWC input (four waves, chunks of eight steps: a gather pays for
+    // itself over longer runs, 56 x 56 x 64 3x3 16.3 us, with four steps 18.6)
+    launch_words_as<HB, LB, MODE, 4, 1, 8, true, EPI_ANY>(p, WH, WL, st, ev_start, ev_stop);
 }
 
 template <int H, int L>
-static void launch_words_hl(bool full, const GemmParams &p, int WH, int WL, hipStream_t st, void *ev_start,
-                            void *ev_stop)
+void launch_nested_gemm_words(bool full, const GemmParams &p, int WH, int WL, hipStream_t st, void *ev_start, void *ev_stop)
 {
-    if (!full) launch_words<H, 0, 0>(p, WH, WL, st, ev_start, ev_stop);
+    if (!full) launch_words<H, L, 0>(p, WH, WL, st, ev_start, ev_stop);
     else if (p.low_signed) launch_words<H, L + 1, 2>(p, WH, WL, st, ev_start, ev_stop);
     else launch_words<H, L, 1>(p, WH, WL, st, ev_start, ev_stop);
 }
-
-void launch_nested_gemm_words(bool full, int h, int l, const GemmParams &p, int WH, int WL, hipStream_t st,
-                              void *ev_start, void *ev_stop)
-{
-    switch (h * 8 + l) {
-    case 7 * 8 + 1: launch_words_hl<7, 1>(full, p, WH, WL, st, ev_start, ev_stop); break;
-    case 6 * 8 + 2: launch_words_hl<6, 2>(full, p, WH, WL, st, ev_start, ev_stop); break;
-    case 5 * 8 + 3: launch_words_hl<5, 3>(full, p, WH, WL, st, ev_start, ev_stop); break;
-    case 4 * 8 + 4: launch_words_hl<4, 4>(full, p, WH, WL, st, ev_start, ev_stop); break;
-    case 3 * 8 + 5: launch_words_hl<3, 5>(full, p, WH, WL, st, ev_start, ev_stop); break;
-    case 2 * 8 + 6: launch_words_hl<2, 6>(full, p, WH, WL, st, ev_start, ev_stop); break;
-    case 5 * 8 + 1: launch_words_hl<5, 1>(full, p, WH, WL, st, ev_start, ev_stop); break;
-    case 4 * 8 + 2: launch_words_hl<4, 2>(full, p, WH, WL, st, ev_start, ev_stop); break;
-    case 3 * 8 + 3: launch_words_hl<3, 3>(full, p, WH, WL, st, ev_start, ev_stop); break;
-    case 2 * 8 + 4: launch_words_hl<2, 4>(full, p, WH, WL, st, ev_start, ev_stop); break;
-    default: break;
-    }
-}
+template void launch_nested_gemm_words<NQ_INST_H, NQ_INST_L>(bool, const GemmParams &, int, int, hipStream_t, void *, void *);
 
 }  // namespace nq

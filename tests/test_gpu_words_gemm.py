@@ -269,3 +269,42 @@ def test_words_conv_resnet_layer_shapes(nq):
         W = weight_from_pages(nq, ph, pl, scale, Cout, K, n, l, False)
         run_conv_both(nq, W, x, geom, w_full, scale, l, True, relu=True, out_int8=True, inv_s_out=1.0 / 0.2)
         run_conv_both(nq, W, x, geom, w_high, scale, l, False, relu=True, out_int8=True, inv_s_out=1.0 / 0.2)
+
+
+def words_case(nq, M, N, K, n, l, signed):
+    w_int, scale = tl.weights(N, K, 0.05, n, seed=M + N + K + l)
+    ph, pl, w_full, w_high = oracle_side(w_int, n, l, signed)
+    return weight_from_pages(nq, ph, pl, scale, N, K, n, l, signed), inputs.uniform_activations((M, K), seed=M + K), w_full, w_high, scale
+
+
+@pytest.mark.parametrize("M,N,K", [(33, 100, 401), (31, 64, 399), (225, 1056, 400), (1, 8, 2003), (95, 4300, 700), (613, 645, 1999)])
+def test_every_block_form(nq, M, N, K):
+    # either side of the launcher's limits, steps that leave the last chunk part empty, rows and columns off the tile
+    for n, l, signed in ((8, 3, False), (6, 2, True)):
+        W, x, w_full, w_high, scale = words_case(nq, M, N, K, n, l, signed)
+        run_both(nq, W, x, w_full, scale, l, True)
+        run_both(nq, W, x, w_high, scale, l, False)
+
+
+@pytest.mark.parametrize("signed", [False, True])
+@pytest.mark.parametrize("n,l", ALL_NL)
+def test_two_row_tiles(nq, n, l, signed):
+    # 400 blocks and K = 2000: two row tiles share the decoding, the last one of them short or (M = 545) not there
+    for M, N, K in ((637, 640, 2000), (545, 709, 2011)):
+        W, x, w_full, _, scale = words_case(nq, M, N, K, n, l, signed)
+        run_both(nq, W, x, w_full, scale, l, True)
+
+
+@pytest.mark.parametrize("signed", [False, True])
+@pytest.mark.parametrize("n,l", ALL_NL)
+def test_gather_in_whole_pieces(nq, n, l, signed):
+    # channels in steps of sixteen: a piece of sixteen bytes never leaves its tap, whatever the chunk it starts
+    for geom in ((1, 9, 8, 48, 40, 3, 3, 1, 1), (1, 7, 9, 176, 33, 3, 3, 2, 1)):
+        B, H, Wd, Cin, Cout, KH, KW, stride, pad = geom
+        K = KH * KW * Cin
+        w_int, scale = tl.weights(Cout, K, inputs.he_sigma(K), n, seed=n + l + Cin)
+        x = inputs.uniform_activations((B, H, Wd, Cin), seed=Cin)
+        ph, pl, w_full, w_high = oracle_side(w_int, n, l, signed)
+        W = weight_from_pages(nq, ph, pl, scale, Cout, K, n, l, signed)
+        run_conv_both(nq, W, x, geom, w_full, scale, l, True)
+        run_conv_both(nq, W, x, geom, w_high, scale, l, False)
