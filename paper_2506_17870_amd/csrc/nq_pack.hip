@@ -1,3 +1,4 @@
+#include <type_traits>
 // Integer weight decomposition and packing kernels (paper Sec. 3.2.1 Eq. 4-5, Alg. 1
 // steps 2-3, Sec. 3.3.4).  All kernels are elementwise streams bound by HBM bandwidth:
 // one byte read and (h + l)/8 bytes written per weight for the fused decompose-and-pack.
@@ -287,25 +288,52 @@ __global__ void __launch_bounds__(256) k_row_absmax(const float *__restrict__ w,
     }
 }
 
-// k_row_absmax and k_pack_dense in one launch, for rows that fit a wave's registers (K <= 256 * NV, 16-byte loads): a
-// wave holds one row, so the channel's scale needs no second look at the weights and no other wave, and its codes go
-// through LDS to the lanes that pack them.  A block has eight rows: a layer of 768 channels is 96 blocks, and eight
-// neighbouring slots of a tile are whole 64-byte sectors of either page even at l = 2.  What bounds it is the read of the
-// fp32 weights and, for a single layer, the launch:
-// 3072 x 768 9.6 us in two launches and 6.1 us in one, 768 x 3072 the same 9.6 us and 8.4 us (9.4 MB: 1.1 to 1.5 TB/s).
-template <int H, int L, int NV>
-__global__ void __launch_bounds__(512) k_quantize_pack(const float *__restrict__ w, int64_t N, int K, int KB, float qmax,
-                                                        float *__restrict__ scale, uint32_t *__restrict__ ph,
-                                                        uint32_t *__restrict__ pl, int sgn)
+// Maximum over a wave, in every lane: permutations inside quads, mirrored halves and rows of sixteen, then the rows' and the
+// halves' exchange; all on the vector ALU (through LDS each step is a round trip of a hundred clocks).
+__device__ __forceinline__ float wave_max(float m)
 {
-    extern __shared__ __attribute__((aligned(16))) uint8_t codes[];   // [8][64 * KB + 16]
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    auto dpp = [](float v, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), decltype(ctrl)::value, 0xf, 0xf, true));
+    };
+    m = fmaxf(m, dpp(m, std::integral_constant<int, 0xB1>{}));        // quad_perm 1 0 3 2
+    m = fmaxf(m, dpp(m, std::integral_constant<int, 0x4E>{}));        // quad_perm 2 3 0 1
+    m = fmaxf(m, dpp(m, std::integral_constant<int, 0x141>{}));       // row_half_mirror
+    m = fmaxf(m, dpp(m, std::integral_constant<int, 0x140>{}));       // row_mirror
+    const auto h = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    m = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+    const auto w = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+    return fmaxf(__uint_as_float(w[0]), __uint_as_float(w[1]));
+}
+
+// k_row_absmax and k_pack_dense in one launch, for rows that fit the registers of WPR waves (K <= 256 * NV * WPR, 16-byte
+// loads): the channel's scale needs no second look at the weights, and the codes go through LDS to the lanes that pack
+// them.  A block has R rows of WPR waves each, which take the row's pieces of 256 columns in turn.  What bounds it is one
+// chain: launch, the read of the fp32 weights, maximum, codes, pages.  A row's waves share the read of a long row and two
+// rows per block make blocks enough (us; eight rows per block of one wave each, before, and now: 3072 x 768 6.7, 6.2;
+// 768 x 3072 9.0, 7.0 (9.4 MB read: 1.5 and 2.0 TB/s of it and the pages, 2.3 us of either the launch); 1024 x 4096 11.3, 8.5;
+// 500 x 2000 6.6, 4.6; 4096 x 4096 21.2, 19.2; 512 x 128 4.1, 3.7).
+template <int H, int L, int NV, int WPR, int R>
+__global__ void __launch_bounds__(64 * WPR * R) k_quantize_pack(const float *__restrict__ w, int64_t N, int K, int KB, float qmax,
+                                                                 float *__restrict__ scale, uint32_t *__restrict__ ph,
+                                                                 uint32_t *__restrict__ pl, int sgn)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t codes[];   // [R][64 * KB + 16]
+    __shared__ float part[R][WPR];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int rs = 64 * KB + 16;
-    const int64_t n0 = (int64_t)blockIdx.x * 8, n = n0 + wave;
+    // The 32 / R blocks of a tile's rows have ids eight apart, i.e. run on one XCD, whose L2 puts their pieces of the pages together.
+    constexpr int SUB = 32 / R;
+    const int g8 = blockIdx.x / (8 * SUB), in8 = blockIdx.x % (8 * SUB);
+    const int64_t n0 = ((int64_t)g8 * 8 + (in8 & 7)) * 32 + (in8 >> 3) * R;
+    if (n0 >= (N + 31) / 32 * 32) return;
+    const int row = wave / WPR, part_of = wave % WPR;
+    const int64_t n = n0 + row;
+    const int c0 = 4 * (lane + 64 * part_of);
     float4 v[NV];
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-        const int c = 4 * (lane + 64 * j);
+        const int c = c0 + 256 * WPR * j;
         v[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
         if (n < N && c < K) v[j] = *reinterpret_cast<const float4 *>(w + n * K + c);
     }
@@ -313,27 +341,51 @@ __global__ void __launch_bounds__(512) k_quantize_pack(const float *__restrict__
 #pragma unroll
     for (int j = 0; j < NV; ++j)
         m = fmaxf(fmaxf(m, fmaxf(fabsf(v[j].x), fabsf(v[j].y))), fmaxf(fabsf(v[j].z), fabsf(v[j].w)));
+    m = wave_max(m);
+    if constexpr (WPR > 1) {
+        if (lane == 0) part[row][part_of] = m;
+        __syncthreads();
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+        for (int i = 0; i < WPR; ++i) m = fmaxf(m, part[row][i]);
+    }
     const float sc = m > 0.0f ? m / qmax : 1.0f;
-    if (lane == 0 && n < N) scale[n] = sc;
+    if (lane == 0 && part_of == 0 && n < N) scale[n] = sc;
     const int qmin = -(1 << (H + L - 1)), qtop = (1 << (H + L - 1)) - 1;
-    auto code = [&](float x) { return (uint32_t)(min(max((int)__builtin_rintf(x / sc), qmin), qtop) & 0xFF); };
+    // Eq. 1 divides: the IEEE quotient, rounded half to even.  Its product with the reciprocal is off by less than
+    // 2^-22 * 128 = 3.1e-5 (both roundings), so it rounds to the same code unless it stands that near to a half; then, and
+    // where the reciprocal or the value is not an ordinary number, the wave divides (eleven instructions per weight).
+    const float inv = 1.0f / sc;
+    bool sure = sc > 1e-30f && sc < 1e30f;
+    uint32_t d[NV];
 #pragma unroll
     for (int j = 0; j < NV; ++j) {
-        const int c = 4 * (lane + 64 * j);
-        uint32_t d = 0;                                   // rows past N and columns past K are zero fields
-        if (n < N && c < K) d = code(v[j].x) | (code(v[j].y) << 8) | (code(v[j].z) << 16) | (code(v[j].w) << 24);
-        if (c < 64 * KB) *reinterpret_cast<uint32_t *>(codes + wave * rs + c) = d;
+        const float x[4] = {v[j].x, v[j].y, v[j].z, v[j].w};
+        d[j] = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float q = x[i] * inv, r = __builtin_rintf(q);
+            sure = sure && fabsf(q - r) < 0.49996f;
+            d[j] |= (uint32_t)((int)fminf(fmaxf(r, (float)qmin), (float)qtop) & 0xFF) << (8 * i);
+        }
+    }
+    if (!__all(sure)) {
+        auto code = [&](float x) { return (uint32_t)(min(max((int)__builtin_rintf(x / sc), qmin), qtop) & 0xFF); };
+#pragma unroll
+        for (int j = 0; j < NV; ++j) d[j] = code(v[j].x) | (code(v[j].y) << 8) | (code(v[j].z) << 16) | (code(v[j].w) << 24);
+    }
+#pragma unroll
+    for (int j = 0; j < NV; ++j) {
+        const int c = c0 + 256 * WPR * j;                       // rows past N and columns past K are zero fields
+        if (c < 64 * KB) *reinterpret_cast<uint32_t *>(codes + row * rs + c) = n < N && c < K ? d[j] : 0u;
     }
     __syncthreads();
-    const int row = tid & 7;
-    for (int u = tid >> 3; u < 2 * KB; u += 64) {         // the row's units of 32 columns
-        const uint4 *src = reinterpret_cast<const uint4 *>(codes + row * rs + 32 * u);
+    const int prow = tid & (R - 1);
+    for (int u = tid / R; u < 2 * KB; u += 64 * WPR) {    // the row's units of 32 columns
+        const uint4 *src = reinterpret_cast<const uint4 *>(codes + prow * rs + 32 * u);
         const uint4 a = src[0], b = src[1];
         const uint32_t A[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
         const uint32_t B[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        pack_slot<H, L, 2>(A, B, (n0 >> 5) * KB + (u >> 1), 32 * (u & 1) + (int)(n0 & 31) + row, ph, pl, sgn);
+        pack_slot<H, L, 2>(A, B, (n0 >> 5) * KB + (u >> 1), 32 * (u & 1) + (int)(n0 & 31) + prow, ph, pl, sgn);
     }
 }
 
@@ -342,15 +394,16 @@ static void launch_quantize_pack(const float *w, int64_t N, int64_t K, int n_bit
                                  hipStream_t s)
 {
     const int KB = (int)ceil_div(K, 64);
-    const dim3 grid((unsigned)(ceil_div(N, 32) * 4)), block(512);
-    const size_t lds = 8 * (64 * (size_t)KB + 16);
     const float qmax = (float)((1 << (n_bits - 1)) - 1);
-#define NQ_QP_LAUNCH(NV)                                                                                            \
-    hipLaunchKernelGGL((k_quantize_pack<H, L, NV>), grid, block, lds, s, w, N, (int)K, KB, qmax, scale, (uint32_t *)ph, \
+#define NQ_QP_LAUNCH(NV, WPR, R)                                                                                    \
+    hipLaunchKernelGGL((k_quantize_pack<H, L, NV, WPR, R>), dim3((unsigned)(ceil_div(ceil_div(N, 32), 8) * 8 * (32 / R))), \
+                       dim3(64 * WPR * R), (size_t)R * (64 * (size_t)KB + 16), s, w, N, (int)K, KB, qmax, scale, (uint32_t *)ph, \
                        (uint32_t *)pl, sgn)
-    if (K <= 1024) NQ_QP_LAUNCH(4);
-    else if (K <= 2048) NQ_QP_LAUNCH(8);
-    else NQ_QP_LAUNCH(16);
+    // (more waves per row or fewer rows per block where rows are short: 0.8 to 1.0 times as fast)
+    if (K <= 512) NQ_QP_LAUNCH(2, 1, 4);
+    else if (K <= 1024) NQ_QP_LAUNCH(2, 2, 2);
+    else if (K <= 2048) NQ_QP_LAUNCH(2, 4, 2);
+    else NQ_QP_LAUNCH(4, 4, 2);
 #undef NQ_QP_LAUNCH
 }
 

@@ -321,3 +321,26 @@ def test_quantise_and_pack_one_launch(nq, N, K):
         assert np.array_equal(host(sc)[:N].view(np.uint32), s.view(np.uint32)) and host(sc)[N] == 0.0
         assert np.array_equal(host(ph)[:ph_ref.size], ph_ref) and np.all(host(ph)[ph_ref.size:] == 0xA5)
         assert np.array_equal(host(pl)[:pl_ref.size], pl_ref) and np.all(host(pl)[pl_ref.size:] == 0xA5)
+
+
+@pytest.mark.parametrize("N,K", [(33, 512), (263, 516), (300, 1024), (290, 2044), (513, 256), (34, 3076), (257, 4096)])
+@pytest.mark.parametrize("n,l", [(8, 2), (8, 5), (6, 1)])
+def test_quantise_and_pack_near_ties(nq, N, K, n, l):
+    # Values at a half step and up to 40 units in the last place either side, for steps that are and are not powers of two: where the
+    # product with the reciprocal cannot decide, the quotient must.  More than eight tiles of rows, rows off the tile.
+    rng = np.random.default_rng(N + K + n)
+    qmax = 127 if n == 8 else 31
+    step = np.where(rng.random(N) < 0.5, 0.25, rng.uniform(1e-3, 2.0, N)).astype(np.float32)
+    w = ((rng.integers(-qmax, qmax, (N, K)) + 0.5).astype(np.float32) * step[:, None])
+    w = (w.view(np.int32) + rng.integers(-40, 41, (N, K))).astype(np.int32).view(np.float32)
+    w[:, 0] = step * qmax
+    wi, s = oracle.quantize(w, n)
+    ph_ref, pl_ref = oracle.decompose_pack(wi, n, l)
+    ph = torch.full((ph_ref.size + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    pl = torch.full((pl_ref.size + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    sc = torch.zeros(N + 1, dtype=torch.float32, device="cuda")
+    nq.nq_quantize_decompose_pack(dev(w), N, K, nq.make_cfg(n, l), sc, ph, pl)
+    torch.cuda.synchronize()
+    assert np.array_equal(host(sc)[:N].view(np.uint32), s.view(np.uint32)) and host(sc)[N] == 0.0
+    assert np.array_equal(host(ph)[:ph_ref.size], ph_ref) and np.all(host(ph)[ph_ref.size:] == 0xA5)
+    assert np.array_equal(host(pl)[:pl_ref.size], pl_ref) and np.all(host(pl)[pl_ref.size:] == 0xA5)
