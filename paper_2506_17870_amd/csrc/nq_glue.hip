@@ -74,7 +74,49 @@ __global__ void __launch_bounds__(256) k_maxpool_i8(const int8_t *__restrict__ x
     y[idx] = (int8_t)best;
 }
 
-// One thread per (image, channel); consecutive threads read consecutive channels.
+__device__ __forceinline__ int8_t avg_code(int sum, float k, float inv_out_scale)
+{
+    const float v = (float)sum * k;
+    float q = rintf(v * inv_out_scale);
+    q = fminf(fmaxf(q, -128.0f), 127.0f);
+    return (int8_t)(int)q;
+}
+
+// Sixteen slices of the pixels for 64 channels of an image, four channels per load (C a multiple of 4, dword-aligned input).  What
+// bounds the pool of a few images is the chain of one thread's loads: 1 x 49 x 2048 with one thread per channel took 13.8 us,
+// with a sixteenth of the pixels each 3.9 (128 images 14.9 and 5.4).
+__global__ void __launch_bounds__(256) k_avgpool_i8_v4(const int8_t *__restrict__ x, int64_t B, int64_t HW, int64_t C,
+                                                        float in_scale, float inv_out_scale, int8_t *__restrict__ y)
+{
+    __shared__ int part[16][64];
+    const int cq = threadIdx.x & 15, slice = threadIdx.x >> 4;
+    const int64_t c0 = (int64_t)blockIdx.x * 64, c = c0 + 4 * cq;
+    const float k = in_scale / (float)HW;
+    for (int64_t b = blockIdx.y; b < B; b += gridDim.y) {
+        int s[4] = {0, 0, 0, 0};
+        if (c < C) {
+            const int8_t *src = x + b * HW * C + c;
+#pragma unroll 4
+            for (int64_t p = slice; p < HW; p += 16) {
+                const int d = *reinterpret_cast<const int *>(src + p * C);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s[i] += (int)(int8_t)((unsigned)d >> (8 * i));
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) part[slice][4 * cq + i] = s[i];
+        __syncthreads();
+        if (threadIdx.x < 64 && c0 + threadIdx.x < C) {
+            int sum = 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) sum += part[i][threadIdx.x];
+            y[b * C + c0 + threadIdx.x] = avg_code(sum, k, inv_out_scale);
+        }
+        __syncthreads();
+    }
+}
+
+// One thread per (image, channel), any C; consecutive threads read consecutive channels.
 __global__ void __launch_bounds__(256) k_avgpool_i8(const int8_t *__restrict__ x, int64_t B, int64_t HW, int64_t C,
                                                      float in_scale, float inv_out_scale, int8_t *__restrict__ y)
 {
@@ -84,10 +126,7 @@ __global__ void __launch_bounds__(256) k_avgpool_i8(const int8_t *__restrict__ x
     int sum = 0;
     for (int64_t p = 0; p < HW; ++p) sum += x[(b * HW + p) * C + c];
     const float k = in_scale / (float)HW;
-    const float v = (float)sum * k;
-    float q = rintf(v * inv_out_scale);
-    q = fminf(fmaxf(q, -128.0f), 127.0f);
-    y[idx] = (int8_t)(int)q;
+    y[idx] = avg_code(sum, k, inv_out_scale);
 }
 
 }  // namespace nq
@@ -123,6 +162,11 @@ extern "C" nq_status nq_avgpool_i8(const int8_t *d_x, int64_t B, int64_t HW, int
     if (HW > (1 << 24)) return NQ_ERR_SHAPE;
     if (B * C == 0) return NQ_OK;
     if (!d_x || !d_y) return NQ_ERR_INVALID_ARG;
+    if (C % 4 == 0 && (reinterpret_cast<uintptr_t>(d_x) & 3u) == 0 && ceil_div(C, 64) <= 0x7fffffffLL) {
+        hipLaunchKernelGGL(k_avgpool_i8_v4, dim3((unsigned)ceil_div(C, 64), (unsigned)(B < 65535 ? B : 65535)), dim3(256), 0,
+                           (hipStream_t)stream, d_x, B, HW, C, in_scale, inv_out_scale, d_y);
+        return launch_status();
+    }
     hipLaunchKernelGGL(k_avgpool_i8, dim3((unsigned)ceil_div(B * C, 256)), dim3(256), 0, (hipStream_t)stream, d_x, B,
                        HW, C, in_scale, inv_out_scale, d_y);
     return launch_status();

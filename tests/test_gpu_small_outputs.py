@@ -344,3 +344,22 @@ def test_quantise_and_pack_near_ties(nq, N, K, n, l):
     assert np.array_equal(host(sc)[:N].view(np.uint32), s.view(np.uint32)) and host(sc)[N] == 0.0
     assert np.array_equal(host(ph)[:ph_ref.size], ph_ref) and np.all(host(ph)[ph_ref.size:] == 0xA5)
     assert np.array_equal(host(pl)[:pl_ref.size], pl_ref) and np.all(host(pl)[pl_ref.size:] == 0xA5)
+
+
+# ---- the stem of a CNN and its last pool on few images --------------------------------------------------------------
+@pytest.mark.parametrize("B,H,W,Cin,N,k,stride,pad", [(1, 56, 60, 3, 64, 7, 2, 3), (2, 40, 200, 1, 80, 3, 1, 1), (1, 33, 36, 8, 40, 3, 1, 0),
+                                                     (3, 19, 12, 4, 33, 7, 1, 3), (1, 12, 8, 10, 32, 3, 2, 1), (24, 64, 64, 3, 48, 7, 2, 3)])
+def test_few_input_channels_on_few_images(nq, B, H, W, Cin, N, k, stride, pad):
+    for n, l, comp in ((8, 2, False), (6, 2, True)):
+        x = inputs.uniform_activations((B, H, W, Cin), seed=W) >> (8 - n)
+        forced(nq, make_case(nq, N, k * k * Cin, n, l, seed=H + N, compensated=comp), x, (k, k, stride, pad), "5", 5)
+
+
+@pytest.mark.parametrize("B,HW,C,off", [(1, 49, 2048, 0), (3, 1, 64, 0), (2, 17, 68, 0), (2, 15, 30, 0), (2, 33, 64, 1), (70, 16, 4, 0)])
+def test_average_pool_in_slices(nq, B, HW, C, off):
+    x = inputs.uniform_activations((B, HW, 1, C), seed=C + HW)
+    buf = torch.zeros(x.size + 4, dtype=torch.int8, device="cuda")
+    buf[off:off + x.size] = dev(x).reshape(-1)
+    y = torch.full((B, C), 77, dtype=torch.int8, device="cuda")
+    nq.nq_avgpool_i8(buf[off:off + x.size], B, HW, C, 0.05, 11.0, y)
+    assert np.array_equal(host(y), oracle.avgpool(x, 0.05, 11.0))
