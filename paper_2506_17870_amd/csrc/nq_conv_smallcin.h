@@ -89,22 +89,27 @@ __global__ void __launch_bounds__(256, 2) k_nested_conv_smallcin(const GemmParam
     __syncthreads();
 
     // ---- gather the lane's weight fragments: filter row kh = bytes [kh*seg, kh*seg + seg) of K ----
+    // (five dwords shifted into place, as for the activations; what they hold past the filter row is masked off.  Byte by byte
+    // the 224 reads were most of the time of a launch over one image.  The last row's reads end in the constants behind it.)
     s_v4i wf[SC_CT][KHC];
     {
+        uint32_t keep[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int left = g.seg - 16 * rg - 4 * i;
+            keep[i] = left >= 4 ? ~0u : (left <= 0 ? 0u : (1u << (8 * left)) - 1u);
+        }
         const int wrow = epi_weight_slot<EPI>(lane) & 31;
 #pragma unroll
         for (int t = 0; t < SC_CT; ++t) {
             const uint8_t *src = wmat + (t * 32 + wrow) * (p.KB * 64);
 #pragma unroll
             for (int kh = 0; kh < KHC; ++kh) {
-                uint32_t d[4] = {0, 0, 0, 0};
+                const int a = kh * g.seg + 16 * rg;
+                const uint32_t *q = reinterpret_cast<const uint32_t *>(src + (a & ~3));
+                const unsigned sh = (unsigned)(a & 3);
 #pragma unroll
-                for (int e = 0; e < 16; ++e) {
-                    const int j = 16 * rg + e;
-                    const uint32_t b = j < g.seg ? src[kh * g.seg + j] : 0u;
-                    d[e >> 2] |= b << (8 * (e & 3));
-                }
-                wf[t][kh] = s_v4i{(int)d[0], (int)d[1], (int)d[2], (int)d[3]};
+                for (int i = 0; i < 4; ++i) wf[t][kh][i] = (int)(__builtin_amdgcn_alignbyte(q[i + 1], q[i], sh) & keep[i]);
             }
         }
     }

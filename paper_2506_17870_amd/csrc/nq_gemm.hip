@@ -136,8 +136,12 @@ bool plan_smallcin(const Geometry &g, const int8_t *d_x, int64_t n_out, SmallCin
     const int row_stride = (d0 + row_bytes + 3) / 4 * 4;
     const int row_dwords = row_bytes / 4;
     const int64_t kb = ceil_div((int64_t)g.KH * seg, 64);
+    const int64_t groups = ceil_div(ceil_div(n_out, 32), 2);
     for (int R = g.Ho; R >= 1; --R) {
         const int IR = (R - 1) * g.stride + g.KH;
+        // as many rows as fit, but for few images fewer, down to a tile of pixels per wave (one 224 x 224 image: 38 blocks of
+        // three rows 19.2 us for the launch, 112 blocks of one 7.7)
+        if (R > 1 && (R - 1) * g.Wo > 96 && images * ceil_div(g.Ho, R) * groups < 512) continue;
         if ((int64_t)IR * row_dwords > 256 * 8) continue;          // dwords a block stages per window
         const int64_t win = ((int64_t)IR * row_stride + 128 + 15) / 16 * 16;   // slack: fragments of the last row read past it
         if (2 * win + 2 * 32 * kb * 64 + 512 > 72 * 1024) continue;   // two blocks per compute unit
@@ -145,7 +149,6 @@ bool plan_smallcin(const Geometry &g, const int8_t *d_x, int64_t n_out, SmallCin
         sg->R = R; sg->RB = (int)ceil_div(g.Ho, R); sg->units = (int)(images * sg->RB);
         sg->IR = IR; sg->seg = seg; sg->d0 = d0; sg->row_stride = row_stride; sg->row_dwords = row_dwords;
         sg->row_bytes = row_bytes; sg->img_bytes = (int)img_bytes; sg->win_bytes = (int)win;
-        const int64_t groups = ceil_div(ceil_div(n_out, 32), 2);
         if (groups > 65535) return false;
         int64_t gx = 512 / groups;
         if (gx < 1) gx = 1;
@@ -261,6 +264,11 @@ bool plan_stat(const Geometry &g, const int8_t *d_x, int64_t N, int64_t K, StatG
         sg->rps = (int)ceil_div(g.M, nslots);
         sg->nslots = (int)ceil_div(g.M, sg->rps);
     }
+    const int64_t row_tiles = ceil_div(g.M, st_bm(sg->wn));
+    sg->tiles = (int)(row_tiles / sg->nslots);
+    sg->over = (int)(row_tiles % sg->nslots);
+    // block ids / 8 are below 2^10 + cgroups: exact with the rounded-up reciprocal
+    sg->cg_magic = sg->cgroups == 1 ? 0u : (unsigned)(((uint64_t(1) << 32) + sg->cgroups - 1) / sg->cgroups);
     sg->strided = strided;
     sg->howo = (int)howo;
     sg->howo_magic = (unsigned)(((uint64_t(1) << 32) + howo - 1) / howo);
