@@ -120,6 +120,8 @@ struct StatGeom {
     int row_step;      // stride * W * Cin: input bytes from one output row to the next
     int col_step;      // stride * Cin
     int x_bytes;       // bytes of the whole input (< 2^31 - 2^16)
+    int tiles, over;   // interleaved: row tiles / nslots and the remainder
+    unsigned cg_magic; // ceil(2^32 / cgroups), 0 for one column group
 };
 
 // Block tile of the stationary-weights GEMM: waves side by side along N (wn of them, 64 columns each), the
