@@ -283,13 +283,13 @@ bool plan_stat(const Geometry &g, const int8_t *d_x, int64_t N, int64_t K, StatG
 }
 
 // Whether the small-output kernel (nq_gemm_slab.h) can take the problem: vector epilogue, 32-bit offsets, dword-aligned
-// rows; a filter needs the 32 bytes a lane reads of a K step inside one tap.
+// rows; a filter whose taps fit 16 bits of index.
 bool slab_ok(const Geometry &g, const int8_t *d_x, int64_t K, int64_t x_bytes, bool general)
 {
     if (general || ((uintptr_t)d_x & 3u) != 0 || g.Cin % 4 != 0) return false;
     if (x_bytes >= 0x7fff0000LL - (1 << 18) || g.M > 65535 * 32) return false;
     const bool one_tap = g.Cin == K && g.pad == 0;
-    return one_tap || (g.Cin % 32 == 0 && g.KH * g.KW * g.KW < 65536);
+    return one_tap || g.KH * g.KW * g.KW < 65536;
 }
 
 int pick_tile(int64_t M, int64_t N)
@@ -557,7 +557,12 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     //   large, K below 400: 700 blocks 2.0, 2120 1.4, 3100 1.15; K below 640: 1000 1.1 to 1.5, 1410 1.2, 1910 0.9, 2180 0.8;
     //   large, longer K, more than 128 columns: 500 blocks 1.4 to 2, 1000 1.1 to 1.7, 1130 1.0 to 1.5, 1460 0.8 to 1;
     //   large, longer K, up to 128 columns (its narrow tiles): 530 blocks 1.2, 680 1.1, 1030 0.8.
-    // Three routes that the tests hold stay as they were: up to 64 columns the generic kernel's own limits (at its call), fp32 columns
+    //   generic, filters of up to 64 columns over multiples of 32 channels: 1300 blocks 2.0, 2860 1.4, 3460 1.05;
+    //   generic, filters over other multiples of 8: K below 256 1000 blocks 2.4, 4600 1.1, 6300 0.9; K below 1024 1500 2.0, 3430 1.5,
+    //   3640 1.1; longer 1100 2.4, 1770 1.6, 1870 1.03 to 1.6, 2900 0.8 to 1.5, and from K = 6144 on 1170 2.2, 1520 0.93;
+    //   generic, filters over other multiples of 4, which it gathers byte by byte: 1.4 to 72, at any number up to 49000;
+    //   few channels (4 or 8 of them; 12 with 7 taps a row go to the generic one): 660 blocks 5.4, 2900 2.8, 6900 1.5 to 2.1.
+    // Three routes that the tests hold stay as they were: GEMMs of up to 64 columns the generic kernel's own limits (at its call), fp32 columns
     // of one 128-wide block of the stationary kernel at K = 128 and filters of four taps above one block per unit, and fp32 outputs
     // of the stationary kernel at K = 64 (500 x 64 -> 256 5.2 us there and 2.7 in small blocks: not all that there is to gain).
     const bool slab_fits = slab_ok(g, d_x, w->K, x_bytes, p.general != 0);
@@ -586,14 +591,19 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     } else if (g.KH * g.KW > 1) {
         WindowGeom wg0;
         size_t lds0 = 0;
+        SmallCinGeom cg0;
         if (plan_window(g, d_x, &wg0, &lds0)) slab_most = 2048;
-        else if (w->N > 64) slab_most = 3072;
+        else if (plan_smallcin(g, d_x, w->N, &cg0)) slab_most = g.Cin % 4 == 0 ? 6500 : 512;
+        else if (g.Cin % 8 == 4) slab_most = INT64_MAX;
+        else if (g.Cin % 32 != 0) slab_most = w->K < 256 ? 4600 : w->K < 1024 ? 3400 : w->K < 6144 ? 1800 : 1280;
+        else slab_most = 3072;
     } else if (w->K == 64 || w->K == 128 || w->K == 256) {
         slab_most = 2048;                              // the stationary kernel's, at any stride
     } else if (w->N > 64) {
         slab_most = 3072;
     }
-    const bool slab_wanted = slab_blocks <= slab_most && (w->K > 64 || (w->K == 64 && p.out_int8)) &&
+    const bool slab_wanted = slab_blocks <= slab_most &&
+                             (w->K > 64 || (w->K == 64 && p.out_int8) || g.KH * g.KW > 1) &&
                              !(streamed && w->K >= 512 && g.M <= 256) && !few_rows;
     auto run_slab = [&](bool for_few_rows) {
         if (!commit()) return NQ_ERR_HIP;
@@ -669,7 +679,8 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     // 0.95 at 2048, 1.2 at 2500.  (A single K step leaves three of four waves without work, and up to 512 blocks that costs
     // nothing: the launch is what takes 4 us.)
     const int64_t slab_limit = w->K <= 128 ? 512 : w->K <= 256 ? 768 : w->K < 352 ? 1024 : w->K < 768 ? 1280 : 2048;
-    if (slab_fits && force == 0 && slab_blocks <= slab_limit) return run_slab(false);
+    const bool split_filter = g.KH * g.KW > 1 && g.Cin % 32 != 0;      // decided above
+    if (slab_fits && force == 0 && !split_filter && slab_blocks <= slab_limit) return run_slab(false);
     const int tile = pick_tile(g.M, w->N);
     if (ceil_div(g.M, NQ_TILE_BM[tile]) > 0x7fffffffLL || ceil_div(w->N, NQ_TILE_BN[tile]) > 65535)
         return NQ_ERR_SHAPE;

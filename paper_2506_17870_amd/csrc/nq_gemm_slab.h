@@ -16,9 +16,11 @@
 //
 // Activations are fetched with dword-aligned 16-byte buffer loads: any K that is a multiple of four serves as a GEMM.
 // What a row's last piece reads past K belongs to the next row (or is out of range) and meets the zero weights the
-// pages are padded with.  CONV: any filter over a multiple of 32 input channels: the 32 bytes a lane needs of a K step
-// are one run of one tap's pixel.  blockIdx.x is the column tile, so that with a multiple of eight column tiles the
-// blocks that read the same weights run on the same XCD.
+// pages are padded with.  CONV: any filter over a multiple of four input channels: the 32 bytes a lane needs of a K step are
+// one run of one tap's pixel (1: multiples of 32 channels), two of 16 bytes (2), four of 8 (3) or eight of 4 (4), each with the
+// tap it lies in: more requests per step, but no staging (28 x 28 x 40 -> 48 3x3 of 5 images 13.0 us in the generic kernel, which
+// walks such rows in pieces, 3.3 here; 21 x 21 x 36 -> 48 of 52 images 102 and 4.1).  blockIdx.x is the column tile, so that
+// with a multiple of eight column tiles the blocks that read the same weights run on the same XCD.
 //
 // Measured in a replayed graph, eight waves with rounds padded to four before and this: 196 x 1024 -> 256 5.4 -> 3.4 us, 14 x 14 x
 // 256 -> 256 3x3 7.7 -> 5.2, 7 x 7 x 512 -> 512 3x3 9.9 -> 7.2, 197 x 3072 -> 768 8.4 -> 6.4, 28 x 28 x 128 -> 512 with a residual
@@ -57,7 +59,7 @@ __device__ __forceinline__ int epi_codes4(const GemmParams &p, const float (&y)[
 // steps per unit: lanes 0-31 hold the first one's weights, lanes 32-63 the second one's).  RG: row groups of NC rows, all
 // multiplied with the same decoded weights.  PD: units in flight per wave.  Four waves per SIMD (the compensated format's
 // longer decoding takes the registers of a fourth).
-template <int H, int L, int FULL, int NC, int RG, int PD, bool CONV>
+template <int H, int L, int FULL, int NC, int RG, int PD, int CONV>
 __global__ void __launch_bounds__(256, FULL == 2 ? 3 : 4) k_nested_gemm_slab(const GemmParams p, const int x_bytes, const unsigned cin_magic)
 {
     constexpr int NWS = 4;                         // waves
@@ -92,7 +94,7 @@ __global__ void __launch_bounds__(256, FULL == 2 ? 3 : 4) k_nested_gemm_slab(con
 #pragma unroll
     for (int r = 0; r < RG; ++r) {
         const int m = m0 + NC * r + (lane & (NC - 1));
-        if constexpr (CONV) {
+        if constexpr (CONV != 0) {
             const int mm = m < M ? m : 0;
             const int HoWo = p.Ho * p.Wo;
             const int b = mm / HoWo, rem = mm - b * HoWo;
@@ -125,29 +127,43 @@ __global__ void __launch_bounds__(256, FULL == 2 ? 3 : 4) k_nested_gemm_slab(con
             for (int c = 0; c < (LP::DW + 3) / 4; ++c) gb_fetch(Q[slot], lrs, LP::DW, c, lv, ls);
         }
         const int k0 = 64 * kb + 32 * g;
-        int kh = 0, kw = 0, ci = 0;
-        if constexpr (CONV) {
-            const int tap = p.Cin == p.K ? 0 : (int)__umulhi((unsigned)k0, cin_magic);
-            kh = (tap * p.kw_magic) >> 16;
-            kw = tap - kh * p.KW;
-            ci = (kh * p.W + kw) * p.Cin + (k0 - tap * p.Cin);
-        }
+        if constexpr (CONV != 0) {
+            // the lane's 32 bytes as one, two, four or eight runs that each lie inside a tap
+            constexpr int RUNS = 1 << (CONV - 1);
 #pragma unroll
-        for (int r = 0; r < RG; ++r) {
-            bool in = real;
-            int at;
-            if constexpr (CONV) {
-                in = k0 < p.K && (unsigned)(ih0[r] + kh) < (unsigned)p.H && (unsigned)(iw0[r] + kw) < (unsigned)p.W;
-                at = x_row[r] + ci;
-            } else {
-                in = in && x_row[r] != NOWHERE;
-                at = x_row[r] + k0;
+            for (int q = 0; q < RUNS; ++q) {
+                const int k = k0 + 32 / RUNS * q;
+                const int tap = p.Cin == p.K ? 0 : (int)__umulhi((unsigned)k, cin_magic);
+                const int kh = (tap * p.kw_magic) >> 16, kw = tap - kh * p.KW;
+                const int ci = (kh * p.W + kw) * p.Cin + (k - tap * p.Cin);
+#pragma unroll
+                for (int r = 0; r < RG; ++r) {
+                    const bool in = k < p.K && (unsigned)(ih0[r] + kh) < (unsigned)p.H && (unsigned)(iw0[r] + kw) < (unsigned)p.W;
+                    const int at = in ? x_row[r] + ci : NOWHERE;
+                    if constexpr (CONV == 4) {
+                        A[slot][r][q >> 2][q & 3] = (int)__builtin_amdgcn_raw_buffer_load_b32(xrs, at, 0, 0);
+                    } else if constexpr (CONV == 3) {
+                        const auto v = __builtin_amdgcn_raw_buffer_load_b64(xrs, at, 0, 0);
+                        A[slot][r][q >> 1][2 * (q & 1)] = (int)v[0];
+                        A[slot][r][q >> 1][2 * (q & 1) + 1] = (int)v[1];
+                    } else {
+#pragma unroll
+                        for (int hf = q; hf < q + 2 / RUNS; ++hf) {
+                            const auto v = __builtin_amdgcn_raw_buffer_load_b128(xrs, at + 16 * (hf - q), 0, 0);
+                            A[slot][r][hf] = e_v4i{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
+                        }
+                    }
+                }
             }
-            at = in ? at : NOWHERE;
+        } else {
 #pragma unroll
-            for (int hf = 0; hf < 2; ++hf) {
-                const auto v = __builtin_amdgcn_raw_buffer_load_b128(xrs, at + 16 * hf, 0, 0);
-                A[slot][r][hf] = e_v4i{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
+            for (int r = 0; r < RG; ++r) {
+                const int at = real && x_row[r] != NOWHERE ? x_row[r] + k0 : NOWHERE;
+#pragma unroll
+                for (int hf = 0; hf < 2; ++hf) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(xrs, at + 16 * hf, 0, 0);
+                    A[slot][r][hf] = e_v4i{(int)v[0], (int)v[1], (int)v[2], (int)v[3]};
+                }
             }
         }
         __builtin_amdgcn_sched_barrier(0);         // requests stay in order: the waits count them
@@ -325,8 +341,11 @@ void launch_nested_gemm_slab(bool full, const GemmParams &p, int x_bytes, hipStr
     } while (0)
 #define NQ_SL_MODES(FULLV)                       \
     do {                                         \
-        if (conv) NQ_SL_LAUNCH(FULLV, true);     \
-        else NQ_SL_LAUNCH(FULLV, false);         \
+        if (!conv) NQ_SL_LAUNCH(FULLV, 0);       \
+        else if (p.Cin % 32 == 0 || p.Cin == p.K) NQ_SL_LAUNCH(FULLV, 1); \
+        else if (p.Cin % 16 == 0) NQ_SL_LAUNCH(FULLV, 2); \
+        else if (p.Cin % 8 == 0) NQ_SL_LAUNCH(FULLV, 3); \
+        else NQ_SL_LAUNCH(FULLV, 4);             \
     } while (0)
     if (full && p.low_signed) NQ_SL_MODES(2); else if (full) NQ_SL_MODES(1); else NQ_SL_MODES(0);
 }

@@ -363,3 +363,32 @@ def test_average_pool_in_slices(nq, B, HW, C, off):
     y = torch.full((B, C), 77, dtype=torch.int8, device="cuda")
     nq.nq_avgpool_i8(buf[off:off + x.size], B, HW, C, 0.05, 11.0, y)
     assert np.array_equal(host(y), oracle.avgpool(x, 0.05, 11.0))
+
+
+# ---- filters over channels in steps of 16, 8 and 4 --------------------------------------------------------------------
+@pytest.mark.parametrize("B,H,W,Cin,N,k,stride,pad,comp", [
+    # taps in two, four and eight runs of a lane's 32 bytes: 16 columns, 32 columns and two row tiles, K ending inside a run's tap
+    (1, 7, 6, 16, 33, 3, 1, 1, False), (2, 9, 9, 48, 64, 3, 2, 1, True), (2, 12, 10, 80, 592, 3, 1, 1, False), (8, 16, 16, 144, 352, 3, 1, 1, True),
+    (1, 7, 6, 8, 33, 3, 1, 1, True), (3, 6, 5, 24, 48, 5, 1, 2, False), (2, 12, 10, 72, 592, 3, 1, 1, True), (8, 16, 16, 120, 352, 3, 1, 1, False),
+    (1, 8, 8, 4, 16, 2, 1, 0, False), (1, 7, 5, 12, 33, 7, 2, 3, True), (2, 12, 10, 36, 592, 3, 1, 1, False), (8, 16, 16, 116, 352, 3, 1, 1, False)])
+def test_filters_of_channels_in_small_steps(nq, B, H, W, Cin, N, k, stride, pad, comp):
+    forced(nq, make_case(nq, N, k * k * Cin, 8, 3, seed=Cin + N, compensated=comp), inputs.uniform_activations((B, H, W, Cin), seed=H),
+           (k, k, stride, pad), "11", 11)
+
+
+@pytest.mark.parametrize("B,H,Cin,N,k,family", [
+    # either side of the limits against the generic kernel, the large one and the one for few channels
+    (1, 56, 36, 40, 3, 11), (20, 112, 36, 32, 3, 11), (46, 56, 24, 32, 3, 11), (47, 56, 24, 32, 3, 1), (34, 56, 56, 32, 3, 11),
+    (35, 56, 56, 32, 3, 1), (18, 56, 120, 32, 3, 11), (19, 56, 120, 32, 3, 1), (32, 14, 272, 160, 3, 11), (33, 14, 272, 192, 3, 4),
+    (66, 56, 8, 32, 3, 11), (67, 56, 8, 32, 3, 5), (3, 56, 2, 32, 3, 5), (31, 56, 32, 32, 3, 11), (32, 56, 32, 32, 3, 1)])
+def test_filters_in_small_steps_or_the_kernel_they_replace(nq, B, H, Cin, N, k, family):
+    # routes alone, on images of zeros: outputs of each kernel are compared elsewhere
+    case = make_case(nq, N, k * k * Cin, 8, 2, seed=Cin + N)
+    cs = nq.nq_conv_shape(B, H, H, Cin, N, k, k, 1, k // 2)
+    bias = inputs.small_floats(N, 0.2, seed=N)
+    epi, _, _ = epi_pair(nq, case, True, (B, H, H), dump=False, s_a=0.02, bias=bias)
+    y = torch.full((B, H, H, N), 77, dtype=torch.float32, device="cuda")
+    nq.nq_conv_full(torch.zeros(B, H, H, Cin, dtype=torch.int8, device="cuda"), cs, case.W.desc, epi, y)
+    torch.cuda.synchronize()
+    assert nq.nq_profile_last_kernel()[0] == family
+    assert torch.equal(y, torch.from_numpy(bias).to(y).expand_as(y))
