@@ -9,10 +9,11 @@
 // there is too little reuse inside a block to pay for a trip through LDS.  The partial sums meet in LDS (integers: any
 // order) and every wave finishes a quarter of the tile, its constants and residual codes requested before the reduction.
 //
-// The links of that chain, a launch that does nothing being 2.3 us of it: what a launch executes is fetched from memory as
-// it goes, so code is kept short (four waves and a loop beat eight or sixteen waves with straight lines per count: 256 x
-// 8192 -> 256 12.9 us against 14.5); requests for units that do not exist are waited for at the end like any other, so
-// a wave of few units makes none; the waits count requests, so nothing that branches stands between them.
+// The links of that chain, a launch that does nothing being 2.3 us of it: every wave's first requests are ahead of all
+// arithmetic, and a wave's decoding is itself a serial chain (8 clocks an instruction with one wave per SIMD), so four waves and a loop
+// of rounds beat eight or sixteen waves with a straight line per count, where the compiler moved the later requests down to their
+// use (256 x 8192 -> 256 12.9 us against 14.5); requests for units that do not exist are waited for at the end like any
+// other, so a wave of few units makes none; the waits count requests, so nothing that branches stands between them.
 //
 // Activations are fetched with dword-aligned 16-byte buffer loads: any K that is a multiple of four serves as a GEMM.
 // What a row's last piece reads past K belongs to the next row (or is out of range) and meets the zero weights the
@@ -221,8 +222,8 @@ __global__ void __launch_bounds__(256, FULL == 2 ? 3 : 4) k_nested_gemm_slab(con
     };
 
     // Up to PD units per wave are straight-line code: everything is requested at once, every wait is an exact count, and
-    // nothing is requested or decoded that does not exist.  The code that a launch runs through once is itself fetched from
-    // memory, so the longer ones are a loop of whole rounds and not one straight line per count.
+    // nothing is requested or decoded that does not exist.  Longer ones are a loop of whole
+    // rounds: in a straight line per count the later requests ended up right before their use.
     const int units = ((p.KB + SPU - 1) / SPU - wave + NWS - 1) / NWS;
     auto few = [&](auto count) {
 #pragma unroll
