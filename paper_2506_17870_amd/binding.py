@@ -358,8 +358,15 @@ def run_layer(full, d_x, sizes, w: nq_weight, act_scale, d_bias, d_residual, res
         if st:
             _check(st, ("nq_gemm_" if gemm else "nq_conv_") + ("full" if full else "part"))
         return
+    run_layer_by_calls(full, d_x, sizes, w, act_scale, d_bias, d_residual, residual_scale, relu, out_int8, inv_out_scale, d_y, stream)
+
+
+def run_layer_by_calls(full, d_x, sizes, w: nq_weight, act_scale, d_bias, d_residual, residual_scale, relu, out_int8,
+                       inv_out_scale, d_y, stream=None):
+    """The same through the four functions of this module, for what the extension hands back and for callers that time or record
+    each call by putting their own in the functions' place."""
     epi = make_epilogue(act_scale, d_bias, d_residual, residual_scale, relu, out_int8, inv_out_scale)
-    if gemm:
+    if isinstance(sizes, int):
         (nq_gemm_full if full else nq_gemm_part)(d_x, sizes, w, epi, d_y, stream)
     else:
         (nq_conv_full if full else nq_conv_part)(d_x, nq_conv_shape(*sizes[:6], *sizes[5:]), w, epi, d_y, stream)
