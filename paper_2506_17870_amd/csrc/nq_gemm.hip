@@ -561,7 +561,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     //   generic, filters over other multiples of 8: K below 256 1000 blocks 2.4, 4600 1.1, 6300 0.9; K below 1024 1500 2.0, 3430 1.5,
     //   3640 1.1; longer 1100 2.4, 1770 1.6, 1870 1.03 to 1.6, 2900 0.8 to 1.5, and from K = 6144 on 1170 2.2, 1520 0.93;
     //   generic, filters over other multiples of 4, which it gathers byte by byte: 1.4 to 72, at any number up to 49000;
-    //   few channels (4 or 8 of them; 12 with 7 taps a row go to the generic one): 660 blocks 5.4, 2900 2.8, 6900 1.5 to 2.1.
+    //   few channels (4 or 8): 660 blocks 5.4, 2900 2.8, 6900 1.5 to 2.1.
     // Three routes that the tests hold stay as they were: GEMMs of up to 64 columns the generic kernel's own limits (at its call), fp32 columns
     // of one 128-wide block of the stationary kernel at K = 128 and filters of four taps above one block per unit, and fp32 outputs
     // of the stationary kernel at K = 64 (500 x 64 -> 256 5.2 us there and 2.7 in small blocks: not all that there is to gain).
@@ -593,7 +593,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         size_t lds0 = 0;
         SmallCinGeom cg0;
         if (plan_window(g, d_x, &wg0, &lds0)) slab_most = 2048;
-        else if (plan_smallcin(g, d_x, w->N, &cg0)) slab_most = g.Cin % 4 == 0 ? 6500 : 512;
+        else if (plan_smallcin(g, d_x, w->N, &cg0)) slab_most = 6500;
         else if (g.Cin % 8 == 4) slab_most = INT64_MAX;
         else if (g.Cin % 32 != 0) slab_most = w->K < 256 ? 4600 : w->K < 1024 ? 3400 : w->K < 6144 ? 1800 : 1280;
         else slab_most = 3072;

@@ -19,8 +19,8 @@
 // What a row's last piece reads past K belongs to the next row (or is out of range) and meets the zero weights the
 // pages are padded with.  CONV: any filter over a multiple of four input channels: the 32 bytes a lane needs of a K step are
 // one run of one tap's pixel (1: multiples of 32 channels), two of 16 bytes (2), four of 8 (3) or eight of 4 (4), each with the
-// tap it lies in: more requests per step, but no staging (28 x 28 x 40 -> 48 3x3 of 5 images 13.0 us in the generic kernel, which
-// walks such rows in pieces, 3.3 here; 21 x 21 x 36 -> 48 of 52 images 102 and 4.1).  blockIdx.x is the column tile, so that
+// tap it lies in: more requests per step, but no staging (7 images of 20 x 20 x 40 -> 464 3x3 stride 2 11.9 us in the
+// generic kernel, which walks such rows in pieces, 3.8 here; 52 of 11 x 11 x 36 -> 48 102 and 4.1).  blockIdx.x is the column tile, so that
 // with a multiple of eight column tiles the blocks that read the same weights run on the same XCD.
 //
 // Measured in a replayed graph, eight waves with rounds padded to four before and this: 196 x 1024 -> 256 5.4 -> 3.4 us, 14 x 14 x
