@@ -44,8 +44,8 @@ RIDGE = MFMA_INT8_PEAK_TOPS * 1e12 / (HBM_PEAK_GBS * 1e9)   # op per byte above 
 TRAFFIC = {   # profiles/gemm_big_conv3x3_b128_counters.txt: FETCH_SIZE x 1.999 KiB, WRITE_SIZE x 1.000 KiB, means per dispatch
     "k_nested_gemm_big<6,2,full,int8 out,TM=6,filter>": dict(sources="617dc069a8210cdf", fetch_bytes=14200896, write_bytes=6422528),
     "k_nested_gemm_big<6,2,part,int8 out,TM=6,filter>": dict(sources="617dc069a8210cdf", fetch_bytes=13006486, write_bytes=6422528),
-    "k_nested_gemm_stat<6,2,full,int8 out,K=256,WN=4>": dict(sources="9afa8e74eec63080", fetch_bytes=34245090, write_bytes=26957926),
-    "k_nested_gemm_stat<6,2,part,int8 out,K=256,WN=4>": dict(sources="9afa8e74eec63080", fetch_bytes=33739487, write_bytes=27041075),
+    "k_nested_gemm_stat<6,2,full,int8 out,K=256,WN=4>": dict(sources="ef8f484b6865b25f", fetch_bytes=34234949, write_bytes=27117150),
+    "k_nested_gemm_stat<6,2,part,int8 out,K=256,WN=4>": dict(sources="ef8f484b6865b25f", fetch_bytes=33717927, write_bytes=27089414),
 }
 KERNEL_SOURCES = {   # what a kernel is made of
     "k_nested_gemm_big": ("nq_gemm_big.h", "nq_epilogue.h", "nq_codec.h", "nq_gemm_kernel.h"),
