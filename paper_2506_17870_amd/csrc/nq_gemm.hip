@@ -605,15 +605,13 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     const bool slab_wanted = slab_blocks <= slab_most &&
                              (w->K > 64 || (w->K == 64 && p.out_int8) || g.KH * g.KW > 1) &&
                              !(streamed && w->K >= 512 && g.M <= 256) && !few_rows;
-    auto run_slab = [&](bool for_few_rows) {
+    auto run_slab = [&]() {
         if (!commit()) return NQ_ERR_HIP;
         g_last_family = 11; g_last_variant = 0;
-        if (for_few_rows) { g_last_family = 6; g_last_variant = 2; }
         NQ_DISPATCH_HL(h, l, launch_nested_gemm_slab, full, p, (int)x_bytes, s, ev0, ev1);
         return launch_status();
     };
-    if (slab_fits && (force == 11 || (force == 0 && slab_wanted))) return run_slab(false);
-    if (slab_fits && force == 0 && few_rows && !few_rows_stream) return run_slab(true);
+    if (slab_fits && (force == 11 || (force == 0 && (slab_wanted || (few_rows && !few_rows_stream))))) return run_slab();
     // short reductions without a filter window: weights stationary in registers, rows streamed
     StatGeom tg;
     // (a K other than 64, 128 or 256 pays for its panels' padding: ahead of the generic kernel on many rows, 78400 x 32 ->
@@ -680,7 +678,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     // nothing: the launch is what takes 4 us.)
     const int64_t slab_limit = w->K <= 128 ? 512 : w->K <= 256 ? 768 : w->K < 352 ? 1024 : w->K < 768 ? 1280 : 2048;
     const bool split_filter = g.KH * g.KW > 1 && g.Cin % 32 != 0;      // decided above
-    if (slab_fits && force == 0 && !split_filter && slab_blocks <= slab_limit) return run_slab(false);
+    if (slab_fits && force == 0 && !split_filter && slab_blocks <= slab_limit) return run_slab();
     const int tile = pick_tile(g.M, w->N);
     if (ceil_div(g.M, NQ_TILE_BM[tile]) > 0x7fffffffLL || ceil_div(w->N, NQ_TILE_BN[tile]) > 65535)
         return NQ_ERR_SHAPE;

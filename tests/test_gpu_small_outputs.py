@@ -113,7 +113,7 @@ def test_small_outputs_every_block_form_filters(nq, B, H, W, Cin, N, k, stride, 
 
 
 @pytest.mark.parametrize("M,N,K,kernel", [
-    (1, 64, 256, (6, 2)), (16, 4128, 4096, (6, 2)), (17, 4128, 4096, (6, 0)), (17, 4096, 4096, (6, 2)), (17, 4128, 4080, (6, 2)),
+    (1, 64, 256, (11, 0)), (16, 4128, 4096, (11, 0)), (17, 4128, 4096, (6, 0)), (17, 4096, 4096, (11, 0)), (17, 4128, 4080, (11, 0)),
     (300, 1040, 768, (11, 0)), (1040, 1024, 1024, (4, 2)), (700, 512, 256, (11, 0)), (2080, 1024, 256, (9, 4)), (640, 128, 1024, (11, 0)),
     (5152, 128, 1024, (4, 7)), (1400, 1008, 120, (11, 0)), (3104, 1024, 120, (1, 1))])
 def test_small_outputs_or_the_kernel_they_replace(nq, M, N, K, kernel):
@@ -143,8 +143,9 @@ def test_small_outputs_by_the_library(nq):
     (20512, 64, 520, False, 1), (32768, 64, 776, True, 11), (32800, 64, 776, True, 1),
     # fp32 columns of one 128-wide block of the stationary kernel: one block per unit
     (2048, 128, 128, False, 11), (2080, 128, 128, False, 9), (2080, 128, 128, True, 11), (2080, 132, 128, False, 11),
-    # up to 64 rows: the kernel for few rows where its split has the fewer idle rounds
-    (33, 256, 704, False, 11), (33, 256, 720, False, 6), (64, 96, 1024, True, 6), (40, 96, 1040, False, 11), (32, 96, 512, False, 6)])
+    # up to 64 rows, whatever the length of the reduction; the kernel for few rows has wide layers over long rows
+    (33, 256, 704, False, 11), (33, 256, 720, False, 11), (64, 96, 1024, True, 11), (40, 96, 1040, False, 11), (32, 96, 512, False, 11),
+    (33, 12320, 2064, True, 6), (33, 12288, 2064, True, 11)])
 def test_small_outputs_where_they_are_the_faster_kernel(nq, M, N, K, i8, family):
     case = make_case(nq, N, K, 8, 2, seed=M + K)
     x = inputs.uniform_activations((M, K), seed=K)
