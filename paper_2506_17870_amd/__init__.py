@@ -9,6 +9,7 @@ without a built library raises ImportError -- there is no fallback path.
 import importlib
 
 __all__ = ["binding", "build", "inputs"]
+_copied = {}                           # what the package holds of the binding's attributes
 
 
 def __getattr__(name):
@@ -19,5 +20,13 @@ def __getattr__(name):
         value = getattr(binding, name)
     except AttributeError:
         raise AttributeError(f"module {__name__!r} has no attribute {name!r}") from None
-    globals()[name] = value            # the next access does not come here (3.5 us, as much as a layer's whole call)
+    globals()[name] = _copied[name] = value        # the next access does not come here (3.5 us, as much as a layer's whole call)
     return value
+
+
+def _forget(*names):
+    """Called by the binding when attributes of its own are replaced: the next access through the package asks it again."""
+    for name in names or list(_copied):
+        value = _copied.pop(name, None)
+        if value is not None and globals().get(name) is value:       # (the caller may have put something else here)
+            del globals()[name]

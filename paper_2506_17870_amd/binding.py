@@ -11,6 +11,8 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
+import types
 
 import torch
 
@@ -500,3 +502,19 @@ class NestedWeight:
             self.close()
         except Exception:
             pass
+
+
+class _Module(types.ModuleType):
+    """This module's type: whoever replaces an attribute here replaces it for the package's users, too."""
+
+    def __setattr__(self, name, value):
+        super().__setattr__(name, value)
+        _forget(name)
+
+    def __delattr__(self, name):
+        super().__delattr__(name)
+        _forget(name)
+
+
+sys.modules[__name__].__class__ = _Module
+_forget()                                # (a module that is loaded again)

@@ -95,3 +95,20 @@ def test_lists_of_weights(nq):
     assert [arr[i].contents.N for i in range(3)] == [1, 2, 3] and len(nq.binding._wlist([])) == 0
     arr[1].contents.N = 7
     assert ws[1].N == 7
+
+
+def test_replaced_functions_are_seen_through_the_package(nq, monkeypatch):
+    own = nq.nq_gemm_full                         # looked up once: the package holds it
+    with monkeypatch.context() as m:
+        m.setattr(nq.binding, "nq_gemm_full", "mine")
+        assert nq.nq_gemm_full == "mine"
+        nq.nq_gemm_full = "here"                  # the package's own stays what its user made it
+        m.setattr(nq.binding, "nq_gemm_full", "other")
+        assert nq.nq_gemm_full == "here"
+        del nq.nq_gemm_full
+    assert nq.nq_gemm_full is own and nq.binding.nq_gemm_full is own
+    nq.binding.extra = 1
+    assert nq.extra == 1
+    del nq.binding.extra
+    with pytest.raises(AttributeError):
+        nq.extra
