@@ -89,7 +89,7 @@ def stamped_forward(model, binding, dx, s_x, full):
     chose, its duration, its operations and its algorithmic bytes (input once, pages once, residual once,
     output once)."""
     recs, names = [], ("nq_conv_full", "nq_conv_part", "nq_gemm_full", "nq_gemm_part")
-    originals = {n: getattr(binding, n) for n in names + ("run_layer",)}
+    originals = {n: getattr(binding, n) for n in names}
     h_bits, l_bits = model.n_bits - model.l_bits, model.l_bits
 
     def stamped(name):
@@ -128,7 +128,6 @@ def stamped_forward(model, binding, dx, s_x, full):
         return call
     for n in names:
         setattr(binding, n, stamped(n))
-    binding.run_layer = binding.run_layer_by_calls       # a layer of the network through the stamped functions
     try:
         model.forward(dx, s_x, full=full)
         import torch

@@ -451,7 +451,7 @@ def c4():
     # per-layer: the time stamps of every GEMM / convolution dispatch of one full-bit forward, by layer shape
     from paper_2506_17870_amd import binding
     recs = []
-    originals = {name: getattr(binding, name) for name in ("nq_conv_full", "nq_gemm_full", "run_layer")}
+    originals = {name: getattr(binding, name) for name in ("nq_conv_full", "nq_gemm_full")}
 
     def stamped(name):
         orig = originals[name]
@@ -462,9 +462,8 @@ def c4():
             orig(*a, **k)
             recs.append((e0, e1, a[1] if name == "nq_conv_full" else None, a[2], bool(a[3].d_residual)))
         return call
-    for name in ("nq_conv_full", "nq_gemm_full"):
+    for name in originals:
         setattr(binding, name, stamped(name))
-    binding.run_layer = binding.run_layer_by_calls
     try:
         model.forward(dx, s_x, full=True)
         torch.cuda.synchronize()

@@ -354,19 +354,24 @@ def run_layer(full, d_x, sizes, w: nq_weight, act_scale, d_bias, d_residual, res
     nq_gemm_full / nq_gemm_part over that many rows, from the values of the descriptors (a layer's two descriptor objects take
     longer to make than its launch)."""
     gemm = isinstance(sizes, int)
-    st = _fast.layer(full, d_x, sizes if gemm else 0, None if gemm else sizes, w, act_scale, d_bias, d_residual, residual_scale, relu,
-                     out_int8, inv_out_scale, d_y, stream if stream is None else _stream(stream))
-    if st >= 0:
-        if st:
-            _check(st, ("nq_gemm_" if gemm else "nq_conv_") + ("full" if full else "part"))
-        return
+_LAYER_CALLS = (nq_conv_full, nq_conv_part, nq_gemm_full, nq_gemm_part)
+
+
+    call = (nq_gemm_full if full else nq_gemm_part) if gemm else (nq_conv_full if full else nq_conv_part)
+    if call in _LAYER_CALLS:             # else somebody times or records the calls: their function gets this one, too
+        st = _fast.layer(full, d_x, sizes if gemm else 0, None if gemm else sizes, w, act_scale, d_bias, d_residual, residual_scale, relu,
+                         out_int8, inv_out_scale, d_y, stream if stream is None else _stream(stream))
+        if st >= 0:
+            if st:
+                _check(st, ("nq_gemm_" if gemm else "nq_conv_") + ("full" if full else "part"))
+            return
     run_layer_by_calls(full, d_x, sizes, w, act_scale, d_bias, d_residual, residual_scale, relu, out_int8, inv_out_scale, d_y, stream)
 
 
 def run_layer_by_calls(full, d_x, sizes, w: nq_weight, act_scale, d_bias, d_residual, residual_scale, relu, out_int8,
                        inv_out_scale, d_y, stream=None):
-    """The same through the four functions of this module, for what the extension hands back and for callers that time or record
-    each call by putting their own in the functions' place."""
+    """The same through the four functions of this module, for what the extension hands back and for callers who put their own in
+    the functions' place."""
     epi = make_epilogue(act_scale, d_bias, d_residual, residual_scale, relu, out_int8, inv_out_scale)
     if isinstance(sizes, int):
         (nq_gemm_full if full else nq_gemm_part)(d_x, sizes, w, epi, d_y, stream)

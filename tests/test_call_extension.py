@@ -112,3 +112,18 @@ def test_replaced_functions_are_seen_through_the_package(nq, monkeypatch):
     del nq.binding.extra
     with pytest.raises(AttributeError):
         nq.extra
+
+
+@pytest.mark.parametrize("full", [True, False])
+@pytest.mark.parametrize("kind", ["conv", "gemm"])
+def test_the_walkers_layers_reach_replaced_functions(nq, monkeypatch, kind, full):
+    w, seen = weight(nq), []
+    name = f"nq_{kind}_{'full' if full else 'part'}"
+    monkeypatch.setattr(nq.binding, name, lambda *a: seen.append(a))
+    for other in ("conv", "gemm"):
+        sizes = 0 if other == "gemm" else (0, 4, 4, 64, 32, 1, 1, 0)
+        nq.run_layer(full, A, sizes, w, 0.5, None, None, 0.0, True, True, 2.0, A, 0)      # empty: no launch
+    assert len(seen) == 1
+    x, what, wd, e, y, stream = seen[0]
+    assert (what == 0 if kind == "gemm" else (what.H, what.Cout) == (4, 32)) and wd is w
+    assert (x, y, stream, e.act_scale, e.relu, e.out_int8, e.inv_out_scale) == (A, A, 0, 0.5, 1, 1, 2.0)
