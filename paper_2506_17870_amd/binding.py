@@ -16,6 +16,8 @@ import types
 
 import torch
 
+from . import _forget
+
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libnq.so")
 
@@ -142,7 +144,11 @@ _current_raw_stream = torch._C._cuda_getCurrentRawStream if hasattr(torch._C, "_
     lambda device: torch.cuda.current_stream(device).cuda_stream)
 
 
-from . import _nqcall as _fast  # noqa: E402  (csrc/nq_call.cpp)
+try:
+    from . import _nqcall as _fast  # (csrc/nq_call.cpp)
+except ImportError as _e:
+    raise ImportError(f"{_HERE}/_nqcall of this interpreter is missing or does not load ({_e}): build it with "
+                      "`python -m paper_2506_17870_amd.build`") from _e
 
 _fast.setup(torch.Tensor, nq_weight, nq_epilogue, nq_conv_shape, nq_cfg,
             getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device), _current_raw_stream,
@@ -348,15 +354,15 @@ def nq_gconv_part(d_x, shape: nq_conv_shape, groups: int, w: nq_weight, epi: nq_
                               _stream(stream)), "nq_gconv_part")
 
 
+_LAYER_CALLS = (nq_conv_full, nq_conv_part, nq_gemm_full, nq_gemm_part)
+
+
 def run_layer(full, d_x, sizes, w: nq_weight, act_scale, d_bias, d_residual, residual_scale, relu, out_int8, inv_out_scale, d_y,
               stream=None):
     """nq_conv_full / nq_conv_part of a square filter, sizes = (B, H, W, Cin, Cout, k, stride, pad), or, with sizes an integer,
     nq_gemm_full / nq_gemm_part over that many rows, from the values of the descriptors (a layer's two descriptor objects take
     longer to make than its launch)."""
     gemm = isinstance(sizes, int)
-_LAYER_CALLS = (nq_conv_full, nq_conv_part, nq_gemm_full, nq_gemm_part)
-
-
     call = (nq_gemm_full if full else nq_gemm_part) if gemm else (nq_conv_full if full else nq_conv_part)
     if call in _LAYER_CALLS:             # else somebody times or records the calls: their function gets this one, too
         st = _fast.layer(full, d_x, sizes if gemm else 0, None if gemm else sizes, w, act_scale, d_bias, d_residual, residual_scale, relu,

@@ -18,7 +18,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libnq.so")
-CALL = os.path.join(HERE, "_nqcall.so")            # the binding's per-call part, a host-only extension (csrc/nq_call.cpp)
+# the binding's per-call part, a host-only extension (csrc/nq_call.cpp), under the name that only this interpreter looks for
+CALL = os.path.join(HERE, "_nqcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 YARDSTICKS = os.path.join(HERE, "nq_yardsticks")   # standalone hardware yardsticks (csrc/nq_yardsticks.hip)
 
 # (h, l): INT(8|h) for l = 1..6 and INT(6|h) for l = 1..4

@@ -127,3 +127,20 @@ def test_the_walkers_layers_reach_replaced_functions(nq, monkeypatch, kind, full
     x, what, wd, e, y, stream = seen[0]
     assert (what == 0 if kind == "gemm" else (what.H, what.Cout) == (4, 32)) and wd is w
     assert (x, y, stream, e.act_scale, e.relu, e.out_int8, e.inv_out_scale) == (A, A, 0, 0.5, 1, 1, 2.0)
+
+
+def test_an_extension_that_is_not_there_is_named(nq):
+    import subprocess
+    import sys
+    code = ("import sys; sys.modules['paper_2506_17870_amd._nqcall'] = None\n"
+            "import paper_2506_17870_amd as nq\n"
+            "try: nq.nq_gemm_full\n"
+            "except ImportError as e: sys.exit(0 if '-m paper_2506_17870_amd.build' in str(e) else 'no hint: %s' % e)\n"
+            "sys.exit('it loads')")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+
+
+def test_the_extension_is_this_interpreters(nq):
+    import sysconfig
+    assert nq.binding._fast.__file__.endswith("_nqcall" + sysconfig.get_config_var("EXT_SUFFIX"))
