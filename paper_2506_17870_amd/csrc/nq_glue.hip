@@ -162,7 +162,13 @@ extern "C" nq_status nq_avgpool_i8(const int8_t *d_x, int64_t B, int64_t HW, int
     if (HW > (1 << 24)) return NQ_ERR_SHAPE;
     if (B * C == 0) return NQ_OK;
     if (!d_x || !d_y) return NQ_ERR_INVALID_ARG;
-    if (C % 4 == 0 && (reinterpret_cast<uintptr_t>(d_x) & 3u) == 0 && ceil_div(C, 64) <= 0x7fffffffLL) {
+    // In slices where a thread's pixels are a chain worth cutting: from 12 pixels on up to 1024 blocks (16384 outputs over 64 channels,
+    // 12 pixels: 3.1 us per channel, 2.7 in slices; 4 pixels 2.6 and 2.7), and beyond, where a pixel costs a block more than the
+    // chain does, from 2048 pixels and channels of a block on (1048576 outputs over 512 channels: 32 pixels 15.8 and 15.0, 16 pixels
+    // 7.0 and 11.1; over 16 channels 100 pixels 55 and 70, 196 pixels 107 and 86).
+    const int64_t slices = B * ceil_div(C, 64), width = C / ceil_div(C, 64);
+    if (C % 4 == 0 && (reinterpret_cast<uintptr_t>(d_x) & 3u) == 0 && ceil_div(C, 64) <= 0x7fffffffLL && HW >= 12 &&
+        (slices <= 1024 || (width >= 16 && HW * width >= 2048))) {
         hipLaunchKernelGGL(k_avgpool_i8_v4, dim3((unsigned)ceil_div(C, 64), (unsigned)(B < 65535 ? B : 65535)), dim3(256), 0,
                            (hipStream_t)stream, d_x, B, HW, C, in_scale, inv_out_scale, d_y);
         return launch_status();

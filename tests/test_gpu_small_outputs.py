@@ -356,7 +356,10 @@ def test_few_input_channels_on_few_images(nq, B, H, W, Cin, N, k, stride, pad):
         forced(nq, make_case(nq, N, k * k * Cin, n, l, seed=H + N, compensated=comp), x, (k, k, stride, pad), "5", 5)
 
 
-@pytest.mark.parametrize("B,HW,C,off", [(1, 49, 2048, 0), (3, 1, 64, 0), (2, 17, 68, 0), (2, 15, 30, 0), (2, 33, 64, 1), (70, 16, 4, 0)])
+@pytest.mark.parametrize("B,HW,C,off", [(1, 49, 2048, 0), (3, 1, 64, 0), (2, 17, 68, 0), (2, 15, 30, 0), (2, 33, 64, 1), (70, 16, 4, 0),
+    # either side of the limits against one thread per channel: pixels, blocks, pixels and channels of many blocks
+    (2, 11, 64, 0), (2, 12, 64, 0), (1024, 12, 68, 0), (512, 12, 68, 0), (513, 31, 68, 0), (1025, 31, 64, 0), (1025, 32, 64, 0),
+    (1025, 128, 16, 0), (1025, 127, 16, 0), (1025, 200, 12, 0), (20000, 1, 64, 0)])
 def test_average_pool_in_slices(nq, B, HW, C, off):
     x = inputs.uniform_activations((B, HW, 1, C), seed=C + HW)
     buf = torch.zeros(x.size + 4, dtype=torch.int8, device="cuda")
