@@ -366,8 +366,8 @@ nq_status nq_profile_next_launch(void *start_event, void *stop_event);
 /* Profiling aid: which kernel the last nq_gemm_* / nq_conv_* / nq_gconv_* launch of this host thread ran:
  * *family as in NQ_TUNE_KERNEL (7 = depthwise / grouped on the matrix cores, 8 = word pages, 10 = other
  * grouped convolutions; 0 before the first launch), *variant for family 10: 2 wider groups on the matrix cores, 1 or 0
- * the direct kernel by dwords or by bytes; for family 6, few rows: 0 a single call, 1 a batch; else the tile height of the
- * large-GEMM kernel (2..7), the tile shape of the generic kernel, the waves along N of the stationary-weights GEMM,
+ * the direct kernel by dwords or by bytes; for family 6, few rows: 0 a single call, 1 a batch; for family 8 the row tiles of a
+ * block (1 or 2); else the tile height of the large-GEMM kernel (2..7), the tile shape of the generic kernel, the waves along N of the stationary-weights GEMM,
  * else 0.  Lets a benchmark group its time stamps by kernel instantiation, as a kernel trace does.  Either pointer may be
  * NULL. */
 nq_status nq_profile_last_kernel(int *family, int *variant);

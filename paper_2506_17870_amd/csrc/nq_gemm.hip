@@ -441,8 +441,8 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         const int lf = low_field_bits(&w->cfg);
         const int WL = (int)ceil_div(w->K, 64 / lf);
         if (!commit()) return NQ_ERR_HIP;
-        g_last_family = 8; g_last_variant = 0;
-        NQ_DISPATCH_HL(h, l, launch_nested_gemm_words, full, p, WH, WL, s, ev0, ev1);
+        g_last_family = 8;
+        NQ_DISPATCH_HL(h, l, launch_nested_gemm_words, full, p, WH, WL, &g_last_variant, s, ev0, ev1);
         return launch_status();
     }
     if (gs > 0 && gs_out > 0) {

@@ -205,10 +205,11 @@ template <int H, int L>
 void launch_nested_gemm_stat(bool full, const GemmParams &p, const StatGeom &g, hipStream_t st, void *ev_start,
                              void *ev_stop);
 
-// GEMM over the paper's word pages (64 / k fields per 64-bit word); WH, WL: words per row of the two pages.
+// GEMM over the paper's word pages (64 / k fields per 64-bit word); WH, WL: words per row of the two pages; *row_tiles: those of
+// a block.
 // Instantiated once per (h, l) by nq_gemm_words.hip.
 template <int H, int L>
-void launch_nested_gemm_words(bool full, const GemmParams &p, int WH, int WL, hipStream_t st, void *ev_start,
+void launch_nested_gemm_words(bool full, const GemmParams &p, int WH, int WL, int *row_tiles, hipStream_t st, void *ev_start,
                               void *ev_stop);
 
 }  // namespace nq

@@ -26,15 +26,20 @@ static void launch_words_as(const GemmParams &p, int WH, int WL, hipStream_t st,
 }
 
 template <int HB, int LB, int MODE>
-static void launch_words(const GemmParams &p, int WH, int WL, hipStream_t st, void *ev_start, void *ev_stop)
+static void launch_words(const GemmParams &p, int WH, int WL, int *row_tiles_of_a_block, hipStream_t st, void *ev_start, void *ev_stop)
 {
     const int64_t blocks = (int64_t)p.NB * ((p.M + 31) / 32);
     // Eight waves share a page's steps where there is at most a block per unit (16 x 8192 -> 8192 30.7 us, with four 42.5; 32 x
     // 1574 -> 5510 9.9, 11.2; with 246 blocks and K = 570 5.4, 5.2; K = 300 5.7, 5.4; with 484 blocks 28.7, 26.3).
     const bool wide = blocks <= 256 && p.K >= 400;
-    // Two row tiles share the decoding of both pages where that is the time and blocks are left (700 x 4000 -> 700 26.3 us, with
-    // one row tile 21.4; 186 x 5292 -> 4643 55.6, 49.8; the higher-bit page alone 276 x 2220 -> 3295 18.1, 21.6).
-    const bool tall = MODE != 0 && p.K >= 2000 && blocks >= 400;
+    // Two row tiles share the decoding of both pages of long rows: a unit's block of them takes 1.7 times as long as one of four waves and
+    // one row tile (full-bit, 9,200 drawn shapes), so they pay where they halve the number of blocks per unit, exactly: not with a
+    // single row tile, whose partner is empty, and not with an odd number that leaves a block over (one row tile, then two, us: 700 x
+    // 4000 -> 700 26.3, 21.4; 186 x 5292 -> 4643 55.6, 49.8; but 4 x 5813 -> 36206 86.8, 144.0; 81 x 7781 -> 5236 66.8, 79.0; the higher-bit page
+    // alone 276 x 2220 -> 3295 18.1, 21.6).  Above four blocks per unit it takes rows of 4000 (two tiles 0.98 of the time at 2000).
+    const int64_t row_tiles = (p.M + 31) / 32;
+    const int64_t per_unit = (blocks + 255) / 256, per_unit_two = ((row_tiles + 1) / 2 * p.NB + 255) / 256;
+    const bool tall = MODE != 0 && 2 * per_unit_two <= per_unit && p.K >= (per_unit <= 4 ? 2000 : 4000);
 #define NQ_WD(NW, RT, CS)                                                                                     \
     do {                                                                                                      \
         if (epi_mode(p) == EPI_F32) launch_words_as<HB, LB, MODE, NW, RT, CS, false, EPI_F32>(p, WH, WL, st, ev_start, ev_stop); \
@@ -48,6 +53,7 @@ static void launch_words(const GemmParams &p, int WH, int WL, hipStream_t st, vo
         }
         if constexpr (MODE != 0) {
             if (tall) {
+                *row_tiles_of_a_block = 2;
                 NQ_WD(8, 2, 2);
                 return;
             }
@@ -61,12 +67,13 @@ static void launch_words(const GemmParams &p, int WH, int WL, hipStream_t st, vo
 }
 
 template <int H, int L>
-void launch_nested_gemm_words(bool full, const GemmParams &p, int WH, int WL, hipStream_t st, void *ev_start, void *ev_stop)
+void launch_nested_gemm_words(bool full, const GemmParams &p, int WH, int WL, int *row_tiles, hipStream_t st, void *ev_start, void *ev_stop)
 {
-    if (!full) launch_words<H, L, 0>(p, WH, WL, st, ev_start, ev_stop);
-    else if (p.low_signed) launch_words<H, L + 1, 2>(p, WH, WL, st, ev_start, ev_stop);
-    else launch_words<H, L, 1>(p, WH, WL, st, ev_start, ev_stop);
+    *row_tiles = 1;
+    if (!full) launch_words<H, L, 0>(p, WH, WL, row_tiles, st, ev_start, ev_stop);
+    else if (p.low_signed) launch_words<H, L + 1, 2>(p, WH, WL, row_tiles, st, ev_start, ev_stop);
+    else launch_words<H, L, 1>(p, WH, WL, row_tiles, st, ev_start, ev_stop);
 }
-template void launch_nested_gemm_words<NQ_INST_H, NQ_INST_L>(bool, const GemmParams &, int, int, hipStream_t, void *, void *);
+template void launch_nested_gemm_words<NQ_INST_H, NQ_INST_L>(bool, const GemmParams &, int, int, int *, hipStream_t, void *, void *);
 
 }  // namespace nq

@@ -308,3 +308,19 @@ def test_gather_in_whole_pieces(nq, n, l, signed):
         W = weight_from_pages(nq, ph, pl, scale, Cout, K, n, l, signed)
         run_conv_both(nq, W, x, geom, w_full, scale, l, True)
         run_conv_both(nq, W, x, geom, w_high, scale, l, False)
+
+
+@pytest.mark.parametrize("M,N,K,tiles", [
+    (637, 640, 2000, 2), (637, 640, 1999, 1), (637, 608, 2000, 2), (545, 709, 2011, 2),     # the length of a row; two blocks per unit, then one
+    (32, 8224, 2000, 1), (3, 12801, 2016, 1), (33, 8192, 2000, 2), (33, 8224, 2000, 1), (96, 4300, 2000, 1),     # a partner that is empty; a tile left over
+    (1000, 1120, 2400, 1), (1000, 1120, 4000, 1), (1024, 1504, 3999, 1), (1024, 1504, 4000, 2)])   # more than four blocks per unit
+def test_two_row_tiles_where_they_halve_the_blocks(nq, M, N, K, tiles):
+    W, x, w_full, w_high, scale = words_case(nq, M, N, K, 8, 3, False)
+    for full, w_ref, want in ((True, w_full, tiles), (False, w_high, 1)):
+        epi = nq.make_epilogue(0.03)
+        y = torch.full((M, N), 77, dtype=torch.float32, device="cuda")
+        (nq.nq_gemm_full if full else nq.nq_gemm_part)(dev(x), M, W.desc, epi, y)
+        torch.cuda.synchronize()
+        assert nq.nq_profile_last_kernel() == (8, want)
+        acc = oracle.gemm_acc(x, w_ref)
+        check_outputs(host(y), None, oracle.epilogue(acc, s_a=0.03, s_w=scale, part_l_bits=0 if full else 3), acc, False)
