@@ -435,8 +435,8 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         if (gather && (g.H > 16000 || g.W > 16000 || g.pad > 255 || g.KH > 255 || g.KW > 255)) return NQ_ERR_SHAPE;
         if ((reinterpret_cast<uintptr_t>(d_x) & 3u) != 0) return NQ_ERR_ALIGN;
         p.conv_big = 0;
-        p.cin_div = 0;
-        p.kw_magic = 0;
+        p.cin_div = g.Cin > 1 ? (unsigned)(((uint64_t(1) << 32) + g.Cin - 1) / g.Cin) : 0u;
+        p.kw_magic = g.KW > 1 ? (int)(unsigned)(((uint64_t(1) << 32) + g.KW - 1) / g.KW) : 0;
         const int WH = (int)ceil_div(w->K, 64 / h);
         const int lf = low_field_bits(&w->cfg);
         const int WL = (int)ceil_div(w->K, 64 / lf);

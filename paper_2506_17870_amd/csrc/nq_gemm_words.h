@@ -18,8 +18,8 @@
 // finishes row tile i.  Like the kernel for few rows it is made for the regime in which the packed weights are the
 // traffic; it takes any M.  What bounds it is the vector ALU: about two instructions per field to move it, four per weight
 // with everything else of a step; beside that the barrier of every chunk, hence chunks of four steps per wave (LDS for
-// five blocks on a unit; with eight steps, the last chunk padded and fp32 outputs stored element by element: 197 x 1000 -> 3000
-// 21.8 -> 14.6 us, 1174 x 126 -> 523 21.6 -> 6.9, 40 x 1000 -> 4000 13.9 -> 9.2, 16 x 8192 -> 8192 37.5 -> 30.7).
+// four blocks on a unit, up to six by the width of the fields; with eight steps, the last chunk padded and fp32 outputs
+// stored element by element: 197 x 1000 -> 3000 21.8 -> 14.6 us, 1174 x 126 -> 523 21.6 -> 6.9, 40 x 1000 -> 4000 13.9 -> 9.2, 16 x 8192 -> 8192 37.5 -> 30.7).
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -126,12 +126,14 @@ __device__ __forceinline__ void words_lds_barrier()
 // the chunks.
 // FIFTH: the sixteen bytes may start inside a dword and reach into a fifth one.
 // CONV: the rows are the output pixels of a convolution and k runs over (kh, kw, ci) of the NHWC input (Sec. 4.1's
-// CNN layers from the paper's own pages): a row is not contiguous in memory, so the staging gathers it, dword by
-// dword when the number of input channels is a multiple of four (a dword then lies inside one filter tap; chunks start on
-// multiples of sixteen, so with a multiple of sixteen the whole piece does: 4 x 28 x 28 x 128 3x3 16.1 us by dwords), else
-// byte by byte; taps outside the image and k >= K are requested out of range and read as zero.  Every row then
-// starts at k = 0 of its own (no alignment to inherit from memory): x_row0 is not used, cv is the geometry.
-template <int KB, bool SGN, bool FIFTH, int NW, int RT, int CS, bool CONV, int EPI>
+// CNN layers from the paper's own pages): a row is not contiguous in memory, so the staging gathers it.  1: dword by
+// dword when the number of input channels is a multiple of four (a dword then lies inside one filter tap), else byte by
+// byte; 2, multiples of sixteen: sixteen bytes at a time (chunks start on multiples of sixteen, so the whole piece lies inside
+// a tap; 4 x 28 x 28 x 128 3x3 16.1 us by dwords).  Taps outside the image and k >= K are requested out of range and read as
+// zero.  Every row then starts at k = 0 of its own (no alignment to inherit from memory): x_row0 is not used, cv is the geometry.
+// (The dwords and the bytes share a kernel: with 16 loads for each of seven pieces and no branch around them the bytes' own
+// needed every register and spilled, four times as long.)
+template <int KB, bool SGN, bool FIFTH, int NW, int RT, int CS, int CONV, int EPI>
 __device__ __forceinline__ void words_page_steps(const __amdgpu_buffer_rsrc_t wrs, int row_off, int W,
                                                  const __amdgpu_buffer_rsrc_t xrs, uint32_t x_row0, int x_rows, int K,
                                                  uint8_t *lds, int tid, int wave, int g, e_v16i (&acc)[RT],
@@ -161,7 +163,7 @@ __device__ __forceinline__ void words_page_steps(const __amdgpu_buffer_rsrc_t wr
         const bool real = r < WC::ROWS;
         st_x[i] = real && r < x_rows ? x_row0 + (uint32_t)(r * K) : NOWHERE;
         st_lds[i] = real ? r * RS + 16 * pi : WC::ROWS * RS;
-        if constexpr (CONV) {
+        if constexpr (CONV != 0) {
             const int64_t m = m0 + r;
             const bool row_ok = real && r < x_rows;
             const int HoWo = cv.Ho * cv.Wo;
@@ -181,7 +183,7 @@ __device__ __forceinline__ void words_page_steps(const __amdgpu_buffer_rsrc_t wr
         for (int i = 0; i < NPT; ++i) {
             const int q = tid + 64 * NW * i;
             const int pi = q % PPR;
-            if constexpr (!CONV) {
+            if constexpr (CONV == 0) {
                 // the row's run starts in the dword that holds its byte k_lo
                 const uint32_t at = st_x[i] == NOWHERE ? NOWHERE : ((st_x[i] + k_lo) & ~3u) + (uint32_t)(16 * pi);
                 const auto v = __builtin_amdgcn_raw_buffer_load_b128(xrs, at, 0, 0);
@@ -190,11 +192,12 @@ __device__ __forceinline__ void words_page_steps(const __amdgpu_buffer_rsrc_t wr
                 // the sixteen bytes k0 .. k0 + 15 of the pixel's row of the implicit GEMM
                 const int k0 = (int)(k_lo & ~3u) + 16 * pi;
                 const int ih0 = st_hw[i] >> 16, iw0 = (int)(int16_t)(st_hw[i] & 0xffff);
-                const int kwc = cv.KW * cv.Cin;
-                int kh = k0 / kwc;
-                const int rem = k0 - kh * kwc;
-                int kw = rem / cv.Cin;
-                int ci = rem - kw * cv.Cin;
+                // (rounded-up reciprocals, exact below 65536, 0 for a divisor of one: a division is forty instructions, two of them a
+                // piece, up to nine pieces a thread)
+                const int tap = cv.cin_div ? (int)__umulhi((unsigned)k0, cv.cin_div) : k0;
+                int ci = k0 - tap * cv.Cin;
+                int kh = cv.kw_magic ? (int)__umulhi((unsigned)tap, (unsigned)cv.kw_magic) : tap;
+                int kw = tap - kh * cv.KW;
                 auto where = [&](int k) -> uint32_t {
                     const bool in = k < K && (unsigned)(ih0 + kh) < (unsigned)cv.H && (unsigned)(iw0 + kw) < (unsigned)cv.W;
                     return in ? (uint32_t)(st_base[i] + (kh * cv.W + kw) * cv.Cin + ci) : NOWHERE;
@@ -207,11 +210,11 @@ __device__ __forceinline__ void words_page_steps(const __amdgpu_buffer_rsrc_t wr
                     }
                 };
                 uint32_t d[4];
-                if ((cv.Cin & 15) == 0) {
+                if constexpr (CONV == 2) {
                     const auto v = __builtin_amdgcn_raw_buffer_load_b128(xrs, where(k0), 0, 0);
 #pragma unroll
                     for (int j = 0; j < 4; ++j) d[j] = v[j];
-                } else if ((cv.Cin & 3) == 0) {
+                } else if (__builtin_expect((cv.Cin & 3) == 0, 1)) {
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         d[j] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(xrs, where(k0 + 4 * j), 0, 0);
@@ -286,12 +289,12 @@ __device__ __forceinline__ void words_page_steps(const __amdgpu_buffer_rsrc_t wr
                     const e_v4i b = WF::decode(Wd[slot].x, Wd[slot].y, group);
                     // the slot's registers are free again: the new request lands in them
                     __builtin_amdgcn_sched_barrier(0);
-                    if constexpr (CONV) request(slot);
+                    if constexpr (CONV != 0) request(slot);
 #pragma unroll
                     for (int r = 0; r < RT; ++r) acc[r] = epi_mfma<EPI>(b, a[r], acc[r]);
                 }
                 t += NW;
-                if constexpr (!CONV) request(slot);
+                if constexpr (CONV == 0) request(slot);
                 // keeps the steps in this order: wait for the oldest, compute, request
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -300,7 +303,7 @@ __device__ __forceinline__ void words_page_steps(const __amdgpu_buffer_rsrc_t wr
     words_lds_barrier();      // the buffers are free for the next page or for the partial sums
 }
 
-template <int KB, bool SGN, int NW, int RT, int CS, bool CONV, int EPI>
+template <int KB, bool SGN, int NW, int RT, int CS, int CONV, int EPI>
 __device__ __forceinline__ void words_page(const __amdgpu_buffer_rsrc_t wrs, int row_off, int W,
                                            const __amdgpu_buffer_rsrc_t xrs, uint32_t x_row0, int x_rows, int K,
                                            uint8_t *lds, int tid, int wave, int g, e_v16i (&acc)[RT], const GemmParams &cv,
@@ -324,7 +327,7 @@ __device__ __forceinline__ void words_page(const __amdgpu_buffer_rsrc_t wrs, int
 // HB: bits of the higher-bit fields.  MODE 0: part-bit; 1: unsigned lower-bit fields of LB = l bits; 2: signed
 // lower-bit fields of LB = l + 1 bits (compensated format, Sec. 3.3.3).  WH, WL: words per row of the pages.
 // NW: waves per block; RT: row tiles of 32; CS: steps per wave and chunk.
-template <int HB, int LB, int MODE, int NW, int RT, int CS, bool CONV, int EPI>
+template <int HB, int LB, int MODE, int NW, int RT, int CS, int CONV, int EPI>
 __global__ void __launch_bounds__(64 * NW) k_nested_gemm_words(const GemmParams p, int WH, int WL)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];   // chunk buffers, then the partial sums

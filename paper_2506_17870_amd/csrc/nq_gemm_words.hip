@@ -15,7 +15,7 @@ static void words_grant_lds(K kernel, size_t lds)
     }
 }
 
-template <int HB, int LB, int MODE, int NW, int RT, int CS, bool CONV, int EPI>
+template <int HB, int LB, int MODE, int NW, int RT, int CS, int CONV, int EPI>
 static void launch_words_as(const GemmParams &p, int WH, int WL, hipStream_t st, void *ev_start, void *ev_stop)
 {
     auto k = k_nested_gemm_words<HB, LB, MODE, NW, RT, CS, CONV, EPI>;
@@ -42,8 +42,8 @@ static void launch_words(const GemmParams &p, int WH, int WL, int *row_tiles_of_
     const bool tall = MODE != 0 && 2 * per_unit_two <= per_unit && p.K >= (per_unit <= 4 ? 2000 : 4000);
 #define NQ_WD(NW, RT, CS)                                                                                     \
     do {                                                                                                      \
-        if (epi_mode(p) == EPI_F32) launch_words_as<HB, LB, MODE, NW, RT, CS, false, EPI_F32>(p, WH, WL, st, ev_start, ev_stop); \
-        else launch_words_as<HB, LB, MODE, NW, RT, CS, false, EPI_ANY>(p, WH, WL, st, ev_start, ev_stop);     \
+        if (epi_mode(p) == EPI_F32) launch_words_as<HB, LB, MODE, NW, RT, CS, 0, EPI_F32>(p, WH, WL, st, ev_start, ev_stop); \
+        else launch_words_as<HB, LB, MODE, NW, RT, CS, 0, EPI_ANY>(p, WH, WL, st, ev_start, ev_stop);     \
     } while (0)
     const bool gather = p.KH != 1 || p.KW != 1 || p.stride != 1 || p.pad != 0;
     if (!gather) {
@@ -61,9 +61,21 @@ static void launch_words(const GemmParams &p, int WH, int WL, int *row_tiles_of_
         NQ_WD(4, 1, 4);
         return;
     }
+#undef NQ_WD
     // a filter other than 1x1 stride 1 gathers its rows from the NHWC input (four waves, chunks of eight steps: a gather pays for
-    // itself over longer runs, 56 x 56 x 64 3x3 16.3 us, with four steps 18.6)
-    launch_words_as<HB, LB, MODE, 4, 1, 8, true, EPI_ANY>(p, WH, WL, st, ev_start, ev_stop);
+    // itself over longer runs, 56 x 56 x 64 3x3 16.3 us, with four steps 18.6).  Whole-row epilogues as for a GEMM: the element-wise
+    // one's sixteen branches a lane are a third of a small layer (13 x 13 x 20 -> 352 3x3, INT(8|5), fp32: the higher-bit page 10.6 us
+    // with it and 7.0, both pages 14.5 and 11.0).
+#define NQ_WD_CONV(CONV)                                                                                      \
+    do {                                                                                                      \
+        const int mode = epi_mode(p);                                                                         \
+        if (mode == EPI_F32) launch_words_as<HB, LB, MODE, 4, 1, 8, CONV, EPI_F32>(p, WH, WL, st, ev_start, ev_stop); \
+        else if (mode == EPI_I8) launch_words_as<HB, LB, MODE, 4, 1, 8, CONV, EPI_I8>(p, WH, WL, st, ev_start, ev_stop); \
+        else launch_words_as<HB, LB, MODE, 4, 1, 8, CONV, EPI_ANY>(p, WH, WL, st, ev_start, ev_stop);         \
+    } while (0)
+    if (p.Cin % 16 == 0) NQ_WD_CONV(2);
+    else NQ_WD_CONV(1);
+#undef NQ_WD_CONV
 }
 
 template <int H, int L>

@@ -324,3 +324,24 @@ def test_two_row_tiles_where_they_halve_the_blocks(nq, M, N, K, tiles):
         assert nq.nq_profile_last_kernel() == (8, want)
         acc = oracle.gemm_acc(x, w_ref)
         check_outputs(host(y), None, oracle.epilogue(acc, s_a=0.03, s_w=scale, part_l_bits=0 if full else 3), acc, False)
+
+
+@pytest.mark.parametrize("geom", [
+    # bytes, dwords and sixteen bytes, stores of sixteen channels and of one; one channel, one column of taps, wide filters, one tap
+    (2, 9, 8, 3, 48, 3, 3, 1, 1), (2, 9, 8, 3, 33, 3, 3, 2, 1), (2, 9, 8, 20, 48, 3, 3, 1, 1), (1, 9, 8, 36, 35, 3, 3, 1, 1),
+    (2, 9, 8, 48, 48, 3, 3, 1, 1), (1, 9, 8, 32, 41, 5, 5, 2, 2), (2, 11, 9, 1, 48, 5, 1, 1, 0), (1, 9, 40, 1, 48, 1, 31, 1, 0),
+    (1, 33, 7, 4, 48, 31, 1, 1, 3), (3, 9, 9, 255, 48, 1, 1, 2, 0), (1, 6, 6, 257, 16, 3, 3, 1, 1), (1, 4, 4, 1, 32, 1, 1, 2, 0)])
+def test_gathers_and_epilogues(nq, geom):
+    B, H, Wd, Cin, Cout, KH, KW, stride, pad = geom
+    K = KH * KW * Cin
+    Ho, Wo = oracle.conv_out_hw(H, Wd, KH, KW, stride, pad)
+    bias = inputs.small_floats(Cout, 0.3, seed=Cout)
+    residual = inputs.uniform_activations((B, Ho, Wo, Cout), seed=K)
+    for n, l, signed in ((8, 3, False), (8, 7 - 1, True), (6, 1, False)):
+        w_int, scale = tl.weights(Cout, K, inputs.he_sigma(K), n, seed=K + l)
+        x = inputs.uniform_activations((B, H, Wd, Cin), seed=K) >> (8 - n)
+        ph, pl, w_full, w_high = oracle_side(w_int, n, l, signed)
+        W = weight_from_pages(nq, ph, pl, scale, Cout, K, n, l, signed)
+        for full, w_ref in ((True, w_full), (False, w_high)):
+            run_conv_both(nq, W, x, geom, w_ref, scale, l, full, bias=bias, relu=True)
+            run_conv_both(nq, W, x, geom, w_ref, scale, l, full, bias=bias, residual=residual, s_r=0.02, out_int8=True, inv_s_out=9.0)
