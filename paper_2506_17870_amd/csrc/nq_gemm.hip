@@ -137,25 +137,26 @@ bool plan_smallcin(const Geometry &g, const int8_t *d_x, int64_t n_out, SmallCin
     const int row_dwords = row_bytes / 4;
     const int64_t kb = ceil_div((int64_t)g.KH * seg, 64);
     const int64_t groups = ceil_div(ceil_div(n_out, 32), 2);
-    for (int R = g.Ho; R >= 1; --R) {
-        const int IR = (R - 1) * g.stride + g.KH;
-        // as many rows as fit, but for few images fewer, down to a tile of pixels per wave (one 224 x 224 image: 38 blocks of
-        // three rows 19.2 us for the launch, 112 blocks of one 7.7)
-        if (R > 1 && (R - 1) * g.Wo > 96 && images * ceil_div(g.Ho, R) * groups < 512) continue;
-        if ((int64_t)IR * row_dwords > 256 * 8) continue;          // dwords a block stages per window
-        const int64_t win = ((int64_t)IR * row_stride + 128 + 15) / 16 * 16;   // slack: fragments of the last row read past it
-        if (2 * win + 2 * 32 * kb * 64 + 512 > 72 * 1024) continue;   // two blocks per compute unit
-        if (images * ceil_div(g.Ho, R) > 0x3fffffffLL) return false;
-        sg->R = R; sg->RB = (int)ceil_div(g.Ho, R); sg->units = (int)(images * sg->RB);
-        sg->IR = IR; sg->seg = seg; sg->d0 = d0; sg->row_stride = row_stride; sg->row_dwords = row_dwords;
-        sg->row_bytes = row_bytes; sg->img_bytes = (int)img_bytes; sg->win_bytes = (int)win;
-        if (groups > 65535) return false;
-        int64_t gx = 512 / groups;
-        if (gx < 1) gx = 1;
-        sg->grid_x = (int)(gx < sg->units ? gx : sg->units);
-        return sg->units > 0;
-    }
-    return false;
+    if (groups > 65535) return false;
+    const int64_t gx = groups > 512 ? 1 : 512 / groups;       // blocks that run at once, two per compute unit
+    auto window = [&](int R) { return (((int64_t)(R - 1) * g.stride + g.KH) * row_stride + 128 + 15) / 16 * 16; };   // slack: fragments of the last row read past it
+    auto fits = [&](int R) {
+        return ((int64_t)(R - 1) * g.stride + g.KH) * row_dwords <= 256 * 8 &&      // dwords a block stages per window
+               2 * window(R) + 2 * 32 * kb * 64 + 512 <= 72 * 1024;                // two blocks per compute unit
+    };
+    // Rows of a unit: as many as fit, but for few images fewer, down to a tile of pixels per wave, as long as every unit has a block and
+    // every block a compute unit of its own (one 224 x 224 image: 38 blocks of three rows 19.2 us for the launch, 112 blocks of one 7.7).
+    // With two blocks on a unit the second one's weights and halo rows cost more than fewer rows give (28 x 83 x 83 x 4 -> 224 3x3 31.8 us,
+    // 41.3 in units of fewer rows; 58 x 18 x 18 x 2 -> 128 7x7 15.1, 14.0 and, two on a unit, 21.2).
+    int R = g.Ho;
+    while (R >= 1 && !fits(R)) --R;
+    if (R < 1 || images * ceil_div(g.Ho, R) > 0x3fffffffLL) return false;
+    while ((int64_t)(R - 1) * g.Wo > 96 && images * ceil_div(g.Ho, R - 1) * groups <= 256) --R;
+    sg->R = R; sg->RB = (int)ceil_div(g.Ho, R); sg->units = (int)(images * sg->RB);
+    sg->IR = (R - 1) * g.stride + g.KH; sg->seg = seg; sg->d0 = d0; sg->row_stride = row_stride; sg->row_dwords = row_dwords;
+    sg->row_bytes = row_bytes; sg->img_bytes = (int)img_bytes; sg->win_bytes = (int)window(R);
+    sg->grid_x = (int)(gx < sg->units ? gx : sg->units);
+    return sg->units > 0;
 }
 
 // Patch shape of the depthwise / grouped kernel: the window of a patch must fit the registers that stage

@@ -349,7 +349,9 @@ def test_quantise_and_pack_near_ties(nq, N, K, n, l):
 
 # ---- the stem of a CNN and its last pool on few images --------------------------------------------------------------
 @pytest.mark.parametrize("B,H,W,Cin,N,k,stride,pad", [(1, 56, 60, 3, 64, 7, 2, 3), (2, 40, 200, 1, 80, 3, 1, 1), (1, 33, 36, 8, 40, 3, 1, 0),
-                                                     (3, 19, 12, 4, 33, 7, 1, 3), (1, 12, 8, 10, 32, 3, 2, 1), (24, 64, 64, 3, 48, 7, 2, 3)])
+                                                     (3, 19, 12, 4, 33, 7, 1, 3), (1, 12, 8, 10, 32, 3, 2, 1), (24, 64, 64, 3, 48, 7, 2, 3),
+                                                     # a unit has fewer rows only as long as every block has a compute unit of its own
+                                                     (11, 46, 46, 4, 128, 3, 1, 1), (40, 32, 32, 2, 96, 7, 2, 3), (2, 64, 64, 3, 400, 3, 1, 1)])
 def test_few_input_channels_on_few_images(nq, B, H, W, Cin, N, k, stride, pad):
     for n, l, comp in ((8, 2, False), (6, 2, True)):
         x = inputs.uniform_activations((B, H, W, Cin), seed=W) >> (8 - n)
