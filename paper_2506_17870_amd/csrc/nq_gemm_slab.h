@@ -321,11 +321,18 @@ void launch_nested_gemm_slab(bool full, const GemmParams &p, int x_bytes, hipStr
     const int units = (p.KB + 3) / 4;              // K steps of a wave of a 32-column block
     // Columns of 16 while they find idle compute units: twice the blocks, half the weights each (us, 32 columns against 16: 14 x
     // 14 x 256 -> 256 3x3 5.4, 5.2; 7 x 7 x 512 -> 512 3x3 7.9, 7.2; 256 x 8192 -> 256 12.6, 11.2; with 112 blocks 5.8 and 5.7,
-    // with 168 6.3 and 9.2; with 128 blocks K = 1024 3.7 and 3.8, K = 4096 8.5 and 7.6).
+    // with 168 6.3 and 9.2; with 128 blocks K = 1024 3.7 and 3.8, K = 4096 8.5 and 7.6).  Not for gathers in smaller steps than 32
+    // channels, whose requests each block makes again: 0.98, 0.94 and 0.89 times as fast in steps of 16, 8 and 4 (1,100 drawn shapes).
     const bool narrow = blocks <= 112 || (blocks <= 128 && p.K >= 2048);
-    // Two row tiles per block where there are blocks enough and the reduction is long (32 x 7 x 7 x 512 -> 512 3x3 23.1, 20.4;
-    // 1000 x 1024 -> 1024 8.5, 8.0; 800 x 4096 -> 1024 22.9, 20.6), unless one of them would be empty (197 x 1024 -> 4096 7.5, 7.7).
-    const bool tall = blocks > 640 && p.K >= 1024 && row_tiles % 2 == 0;
+    // Two row tiles per block, which decode the weights once for both, where that halves the blocks of the busiest unit exactly and rows are
+    // long: 1.07 to 1.14 times as fast as one on 2,000 drawn shapes (32 x 7 x 7 x 512 -> 512 3x3 23.1, 20.4; 1000 x 1024 -> 1024 8.5, 8.0;
+    // 800 x 4096 -> 1024 22.9, 20.6), where it does not 0.87 to 0.97 (4003 x 4856 -> 168 24.6, 27.5; 700 blocks take three rounds of
+    // units, half as many blocks two of twice the length).  A last block with one row tile is no loss from sixteen row tiles on (197 x
+    // 1024 -> 4096, seven of them, 7.5, 7.7).  The gathers in steps of 8 and 4 channels are 0.73 to 0.98 times as fast with two, that in
+    // steps of 16 is from K = 2048 on (0.91; below 1.05), and over rows beyond 8192 so is the filter's (0.94).
+    const int64_t per_unit = (blocks + 255) / 256, per_unit_two = ((row_tiles + 1) / 2 * p.NB + 255) / 256;
+    const bool halves = blocks > 640 && p.K >= 1024 && (row_tiles % 2 == 0 || row_tiles >= 16) &&
+                        (2 * per_unit_two <= per_unit || per_unit > 8);
     // Three or four units in flight per wave, whichever leaves whole rounds (K = 1024: 8.6 with three, 7.5 with four; K = 1536:
     // 8.7 and 9.5: more registers, fewer blocks on a unit).
     const bool three = units % 3 == 0 || units < 3;
@@ -335,9 +342,19 @@ void launch_nested_gemm_slab(bool full, const GemmParams &p, int x_bytes, hipStr
                  ev_start, ev_stop, p, x_bytes, cin_magic)
 #define NQ_SL_LAUNCH(FULLV, CONVV)                           \
     do {                                                     \
-        if (narrow) NQ_SL_ONE(FULLV, 16, 2, 3, CONVV);       \
-        else if (tall) NQ_SL_ONE(FULLV, 32, 2, 2, CONVV);    \
-        else if (three) NQ_SL_ONE(FULLV, 32, 1, 3, CONVV);   \
+        if constexpr (CONVV <= 1) {                          \
+            if (narrow) {                                    \
+                NQ_SL_ONE(FULLV, 16, 2, 3, CONVV);           \
+                break;                                       \
+            }                                                \
+        }                                                    \
+        if constexpr (CONVV <= 2) {                          \
+            if (halves && p.K < (CONVV == 0 ? 0x7fffffff : CONVV == 1 ? 8192 : 2048)) { \
+                NQ_SL_ONE(FULLV, 32, 2, 2, CONVV);           \
+                break;                                       \
+            }                                                \
+        }                                                    \
+        if (three) NQ_SL_ONE(FULLV, 32, 1, 3, CONVV);        \
         else NQ_SL_ONE(FULLV, 32, 1, 4, CONVV);              \
     } while (0)
 #define NQ_SL_MODES(FULLV)                       \

@@ -100,7 +100,8 @@ def test_small_outputs_every_nesting(nq, n, l, compensated):
 @pytest.mark.parametrize("M,N,K", [
     (200, 600, 64), (199, 604, 260), (197, 592, 580), (193, 608, 1020),      # 32 columns: one to four units per wave, waves with none
     (200, 600, 1100), (224, 592, 1536), (200, 596, 1796),                    # rounds of three and four, a last one of one to four
-    (113, 1024, 2048), (2047, 352, 1024), (2048, 340, 1284), (2033, 352, 1540)])   # 16 columns of 128 blocks; two row tiles
+    (113, 1024, 2048), (2047, 352, 1024), (2048, 340, 1284), (2033, 352, 1540),   # 16 columns of 128 blocks; two row tiles
+    (1544, 512, 1028), (480, 1440, 1300), (4003, 168, 1200)])                # ... the last block's second one empty; blocks that do not halve
 def test_small_outputs_every_block_form(nq, M, N, K):
     forced(nq, make_case(nq, N, K, 8, 2, seed=M + K), inputs.uniform_activations((M, K), seed=K), None, "11", 11)
 
