@@ -523,11 +523,12 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     // large-GEMM kernel's tiles, 128 columns at the least, would be half empty.  (Up to 128 channels they went there
     // too while the large kernel had 256-column tiles only; with its 128 x 128 variant, 3x3, 28x28x128 -> 128 at
     // batch 128 takes 29 us against 42 us, and at stride 2 31 us against 59 us.)
+    const bool filter = g.KH * g.KW > 1;
+    WindowGeom wg;
+    size_t lds = 0;
+    const bool windowed = filter && plan_window(g, d_x, &wg, &lds);
     {
-        WindowGeom wg0;
-        size_t lds0 = 0;
-        if (conv_gemm && w->N <= 64 && g.stride == 1 && g.KH * g.KW > 1 && plan_window(g, d_x, &wg0, &lds0))
-            big_wanted = false;
+        if (conv_gemm && w->N <= 64 && g.stride == 1 && windowed) big_wanted = false;
         // With the element-wise epilogue (ragged N and the like) the large kernel runs one block per unit, and over channel
         // counts that are no power of two it is ahead of the generic kernel from K = 640 on (15000 rows, 250 columns: K = 272
         // 42.1 us there and 45.6 here, K = 720 51.9 and 48.0), with several column tiles if they are nine tenths filled (15000 x
@@ -539,7 +540,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
             const int64_t col_tiles = ceil_div(w->N, 256);
             const bool filled = col_tiles == 1 || w->N * 10 >= col_tiles * 256 * 9;
             if (w->K < 640 || !(filled || (w->K >= 1024 && ceil_div(g.M, 128) * col_tiles <= 128))) big_wanted = false;
-            if (plan_window(g, d_x, &wg0, &lds0) && (wg0.CK > 64 || w->K < 2304 || g.M > 4096)) big_wanted = false;
+            if (windowed && (wg.CK > 64 || w->K < 2304 || g.M > 4096)) big_wanted = false;
         }
         // Short reductions over such channel counts stay with the generic kernel where its 128 x 256 tiles fill the units
         // once (12032 x 320 -> 336 10.6 us there, 12.1 here; with half or twice as many tiles 0.7 to 0.98 times the time here).
@@ -550,61 +551,69 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     }
     // Outputs too small to fill the chip with large tiles: 32 x 32 blocks that split K over their waves (nq_gemm_slab.h).  They
     // are ahead of every other kernel up to several blocks per compute unit; how many depends on which kernel would run
-    // instead.  Limits from 380 drawn shapes with both sides forced, times of the other kernel over theirs:
-    //   stationary (K = 64, 128, 256): 500 blocks 2.0, 1100 1.5, 2050 1.1 to 1.2, 3000 0.94 to 1.15;
-    //   generic: 850 blocks 2.3, 1700 1.7, 3000 1.2 to 1.5, 4300 0.98 to 1.7, 4800 0.8 to 1.2;
+    // instead.  Limits from 20,000 drawn shapes with both sides timed (three nestings, both modes, all outputs), times of the other
+    // kernel over theirs, median and worst:
+    //   stationary (K = 64, 128, 256): 500 blocks 1.7 to 2, 1100 1.5, 2050 1.2 (1.08), 3000 0.95; fp32 in rows of no whole 16-byte
+    //   stores 1280 1.1 (1.04), 1500 0.9, 2050 0.83;
+    //   generic: 1000 blocks 2.3, 2000 1.7, 3000 1.4 (1.11), 4500 1.1 (0.84); such fp32 rows, K below 128: 2560 1.08, 2800 0.95;
     //   windowed: 400 blocks 2.8, 1250 3.6, 1770 1.2, 2700 1.0;
     //   register-stationary 3x3: 400 blocks 1.25, 1090 1.1, 1470 0.9;
-    //   large, K below 400: 700 blocks 2.0, 2120 1.4, 3100 1.15; K below 640: 1000 1.1 to 1.5, 1410 1.2, 1910 0.9, 2180 0.8;
-    //   large, longer K, more than 128 columns: 500 blocks 1.4 to 2, 1000 1.1 to 1.7, 1130 1.0 to 1.5, 1460 0.8 to 1;
-    //   large, longer K, up to 128 columns (its narrow tiles): 530 blocks 1.2, 680 1.1, 1030 0.8.
-    //   generic, filters of up to 64 columns over multiples of 32 channels: 1300 blocks 2.0, 2860 1.4, 3460 1.05;
-    //   generic, filters over other multiples of 8: K below 256 1000 blocks 2.4, 4600 1.1, 6300 0.9; K below 1024 1500 2.0, 3430 1.5,
-    //   3640 1.1; longer 1100 2.4, 1770 1.6, 1870 1.03 to 1.6, 2900 0.8 to 1.5, and from K = 6144 on 1170 2.2, 1520 0.93;
+    //   large, K below 400: 700 blocks 1.8, 1700 1.3 (1.01), 2050 1.2 (0.89); K below 640: 1000 1.5, 1280 1.3 (1.19), 1400 1.1 (0.92);
+    //   large, longer K, more than 128 columns: 500 blocks 2, 1000 1.3 to 1.4 (0.98), 1150 1.1 (0.84); K from 1280 on with activations
+    //   of more than 8 MB, which the column tiles read again from memory: 770 1.3 (0.94), 950 0.74 to 1.1;
+    //   large, longer K, up to 128 columns (its narrow tiles): 512 blocks 1.65 (1.1), 640 1.3 (1.0); 560 with more than 8 MB 0.9;
+    //   K below 640 900 1.6, 1000 1.3 (0.92);
+    //   generic, filters over multiples of 32 channels: 2860 blocks 1.4, 3460 1.3 (1.0); over other multiples of 8: K below 64 3000
+    //   1.2, 4400 0.8; K below 256 4600 1.5 (steps of 16: 4000 1.2 (1.02), 4600 1.0 (0.88)); K below 1024 3400 1.2 (1.02); longer 1500 1.9
+    //   (1.28), 2000 1.35 (0.83), and from K = 6144 on 1170 2.2, 1520 0.93;
     //   generic, filters over other multiples of 4, which it gathers byte by byte: 1.4 to 72, at any number up to 49000;
     //   few channels (4 or 8): 660 blocks 5.4, 2900 2.8, 6900 1.5 to 2.1.
-    // Three routes that the tests hold stay as they were: GEMMs of up to 64 columns the generic kernel's own limits (at its call), fp32 columns
-    // of one 128-wide block of the stationary kernel at K = 128 and filters of four taps above one block per unit, and fp32 outputs
-    // of the stationary kernel at K = 64 (500 x 64 -> 256 5.2 us there and 2.7 in small blocks: not all that there is to gain).
+    // Not used, because what runs there is held by tests: fp32 columns of one 128-wide block of the stationary kernel at K = 128 and
+    // filters of four taps above one block per unit, filters of K >= 512 over up to 256 pixels that the register-stationary kernel
+    // takes (16 x 16 x 64 -> 96 3x3 4.3 us there, 2.8 here; with weights that no cache holds 5.2 and 3.4), and fp32 outputs of the
+    // stationary kernel at K = 64, where small blocks are ahead up to 2500 blocks (500 x 64 -> 256 5.2 us there, 2.7 here).
     const bool slab_fits = slab_ok(g, d_x, w->K, x_bytes, p.general != 0);
     const bool skinny_ok = g.KH == 1 && g.KW == 1 && g.stride == 1 && g.pad == 0 && g.M <= 64 && w->K % 16 == 0 &&
                            aligned16(d_x) && ceil_div(w->N, 32) <= 0x7fffffffLL;
     const int64_t slab_blocks = ceil_div(g.M, 32) * ceil_div(w->N, 32);
-    const bool stat_columns = w->K == 128 && w->N > 64 && w->N <= 128 && !p.out_int8;
+    const bool stat_shape = !filter && g.pad == 0 && (w->K == 64 || w->K == 128 || w->K == 256);
+    const bool stat_columns = stat_shape && w->K == 128 && w->N > 64 && w->N <= 128 && !p.out_int8;
+    // fp32 rows that are no whole number of 16-byte stores, which small blocks store element by element
+    const bool ragged = !p.out_int8 && w->N % 4 != 0;
+    // activations that several XCDs' caches would have to read again for every column tile
+    const bool wide_rows = x_bytes > (int64_t(8) << 20);
     // Few rows, weights read once: their own kernel (nq_gemm_skinny.h) streams the pages of wide layers with long rows best
     // (64 x 8192 -> 8192 23.4 us there, 29.2 in small blocks; 32 x 8192 -> 6144 0.91 of the time; 56 x 2608 -> 14976 0.96);
     // everything else of them small blocks take faster (16 x 4096 -> 4096 9.5 there, 7.6 here; 8 x 512 -> 512 3.4, 2.5; 64 x
     // 1536 -> 8192 1.2 times; up to 16 rows 1.03 to 1.8 times for any size).
     const bool few_rows = skinny_ok && w->K >= 256 && (g.M <= 32 || slab_blocks > 256 || (p.KB >= 12 && p.KB <= 16));
     const bool few_rows_stream = g.M > 16 && ((w->N > 4096 && w->K >= 4096) || (w->N > 12288 && w->K >= 2048));
-    // Filters the register-stationary kernel takes (3x3 over 64 channels, 2x2 over 64 and 128) stay there from K = 512 on up to 256
-    // pixels, where it meets cold weights faster (8 x 8 x 64 -> 460 4.2 us there, 4.8 in small blocks as they were).
-    StreamGeom few;
-    int few_blocks = 0;
-    const bool streamed = g.KH * g.KW > 1 && plan_rowstream(g, d_x, w->N, &few, &few_blocks);
+    StreamGeom sg;
+    int grid_x = 0;
+    const bool streams = plan_rowstream(g, d_x, w->N, &sg, &grid_x), streamed = filter && streams;
+    SmallCinGeom cg;
+    const bool few_channels = filter && plan_smallcin(g, d_x, w->N, &cg);
     int64_t slab_most = 512;
     if (stat_columns) {
         slab_most = 256;
     } else if (streamed) {
         slab_most = g.KH * g.KW == 9 ? 1024 : 256;
     } else if (big_ok && big_wanted) {
-        slab_most = w->K < 400 ? 2048 : w->N <= 128 ? (w->K < 640 ? 1024 : 640) : (w->K < 640 ? 1408 : 1024);
-    } else if (g.KH * g.KW > 1) {
-        WindowGeom wg0;
-        size_t lds0 = 0;
-        SmallCinGeom cg0;
-        if (plan_window(g, d_x, &wg0, &lds0)) slab_most = 2048;
-        else if (plan_smallcin(g, d_x, w->N, &cg0)) slab_most = 6500;
+        if (w->N <= 128) slab_most = w->K < 400 ? 2048 : w->K < 640 ? 896 : wide_rows ? 512 : 640;
+        else slab_most = w->K < 400 ? 1792 : w->K < 640 ? 1280 : w->K >= 1280 && wide_rows ? 768 : 1024;
+    } else if (filter) {
+        if (windowed) slab_most = 2048;
+        else if (few_channels) slab_most = 6500;
         else if (g.Cin % 8 == 4) slab_most = INT64_MAX;
-        else if (g.Cin % 32 != 0) slab_most = w->K < 256 ? 4600 : w->K < 1024 ? 3400 : w->K < 6144 ? 1800 : 1280;
+        else if (g.Cin % 32 != 0) slab_most = w->K < 64 ? 3072 : w->K < 256 ? (g.Cin % 16 == 0 ? 4096 : 4600) : w->K < 1024 ? 3400 : w->K < 6144 ? 1800 : 1280;
         else slab_most = 3072;
-    } else if (w->K == 64 || w->K == 128 || w->K == 256) {
-        slab_most = 2048;                              // the stationary kernel's, at any stride
+    } else if (stat_shape) {
+        slab_most = ragged ? 1280 : 2048;              // at any stride
     } else if (w->N > 64) {
-        slab_most = 3072;
+        slab_most = ragged && w->K < 128 ? 2560 : 3072;
     }
     const bool slab_wanted = slab_blocks <= slab_most &&
-                             (w->K > 64 || (w->K == 64 && p.out_int8) || g.KH * g.KW > 1) &&
+                             (w->K > 64 || (w->K == 64 && p.out_int8) || filter) &&
                              !(streamed && w->K >= 512 && g.M <= 256) && !few_rows;
     auto run_slab = [&]() {
         if (!commit()) return NQ_ERR_HIP;
@@ -645,25 +654,20 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         NQ_DISPATCH_HL(h, l, launch_nested_gemm_skinny, full, p, s, ev0, ev1);
         return launch_status();
     }
-    SmallCinGeom cg;
-    if ((force == 0 || force == 5) && plan_smallcin(g, d_x, w->N, &cg)) {
+    if ((force == 0 || force == 5) && few_channels) {
         if (!commit()) return NQ_ERR_HIP;
         g_last_family = 5; g_last_variant = 0;
         NQ_DISPATCH_HL(h, l, launch_nested_conv_smallcin, full, p, cg, s, ev0, ev1);
         return launch_status();
     }
-    StreamGeom sg;
-    int grid_x = 0;
-    if ((force == 0 || force == 3) && plan_rowstream(g, d_x, w->N, &sg, &grid_x)) {
+    if ((force == 0 || force == 3) && streams) {
         if ((int64_t)(grid_x + 7) * ceil_div(w->N, 32) > 0x7fffffffLL) return NQ_ERR_SHAPE;
         if (!commit()) return NQ_ERR_HIP;
         g_last_family = 3; g_last_variant = 0;
         NQ_DISPATCH_HL(h, l, launch_nested_conv_rowstream, full, p, sg, grid_x, s, ev0, ev1);
         return launch_status();
     }
-    WindowGeom wg;
-    size_t lds = 0;
-    if ((force == 0 || force == 2) && plan_window(g, d_x, &wg, &lds)) {
+    if ((force == 0 || force == 2) && windowed) {
         const int64_t blocks_x = (g.M / ((int64_t)g.Ho * g.Wo)) * wg.RB;
         if (blocks_x > 0x7fffffffLL || ceil_div(w->N, 64) > 65535) return NQ_ERR_SHAPE;
         if (!commit()) return NQ_ERR_HIP;
@@ -671,15 +675,14 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         NQ_DISPATCH_HL(h, l, launch_nested_conv_window, full, 0, p, wg, lds, s, ev0, ev1);
         return launch_status();
     }
-    // What is left would go to the generic kernel, which walks K one step at a time: small blocks again, up to the number
-    // at which both take as long.  Both sides measured on N = 16 to 1000, time against the generic kernel's, worst of
-    // them at the limit and at the next number up: K = 16 to 96 0.9 to 1.0 at 512 blocks, 1.3 at 640; K = 144 to 256 0.93
-    // at 768, 1.2 at 900; K = 272 to 320 0.92 at 1024, 1.05 at 1150; K = 352 to 720 0.92 at 1280, 1.15 at 1450; K = 776 to 2008
-    // 0.95 at 2048, 1.2 at 2500.  (A single K step leaves three of four waves without work, and up to 512 blocks that costs
-    // nothing: the launch is what takes 4 us.)
+    // GEMMs of up to 64 columns or of one K step at most are left (the others had their limit above) and would go to the generic
+    // kernel, which walks K one step at a time: small blocks again, up to the number at which both take as long.  Both sides measured
+    // on N = 16 to 64 and, for one step, to 1000, time against the generic kernel's, worst of them at the limit and at the next number
+    // up: K = 16 to 96 0.9 to 1.0 at 512 blocks, 1.3 at 640; K = 144 to 256 0.93 at 768, 1.2 at 900; K = 272 to 320 0.92 at 1024, 1.05
+    // at 1150; K = 352 to 720 0.92 at 1280, 1.15 at 1450; K = 776 to 2008 0.95 at 2048, 1.2 at 2500.  (A single K step leaves three of
+    // four waves without work, and up to 512 blocks that costs nothing: the launch is what takes the time.)
     const int64_t slab_limit = w->K <= 128 ? 512 : w->K <= 256 ? 768 : w->K < 352 ? 1024 : w->K < 768 ? 1280 : 2048;
-    const bool split_filter = g.KH * g.KW > 1 && g.Cin % 32 != 0;      // decided above
-    if (slab_fits && force == 0 && !split_filter && slab_blocks <= slab_limit) return run_slab();
+    if (slab_fits && force == 0 && !filter && slab_blocks <= slab_limit) return run_slab();
     const int tile = pick_tile(g.M, w->N);
     if (ceil_div(g.M, NQ_TILE_BM[tile]) > 0x7fffffffLL || ceil_div(w->N, NQ_TILE_BN[tile]) > 65535)
         return NQ_ERR_SHAPE;

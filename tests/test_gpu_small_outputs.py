@@ -146,7 +146,13 @@ def test_small_outputs_by_the_library(nq):
     (2048, 128, 128, False, 11), (2080, 128, 128, False, 9), (2080, 128, 128, True, 11), (2080, 132, 128, False, 11),
     # up to 64 rows, whatever the length of the reduction; the kernel for few rows has wide layers over long rows
     (33, 256, 704, False, 11), (33, 256, 720, False, 11), (64, 96, 1024, True, 11), (40, 96, 1040, False, 11), (32, 96, 512, False, 11),
-    (33, 12320, 2064, True, 6), (33, 12288, 2064, True, 11)])
+    (33, 12320, 2064, True, 6), (33, 12288, 2064, True, 11),
+    # fp32 rows that leave element by element: the stationary kernel and, for short rows, the generic one sooner
+    (1280, 1021, 128, False, 11), (1312, 1021, 128, False, 9), (1312, 1024, 128, False, 11), (2560, 1021, 72, False, 11), (2592, 1021, 72, False, 1),
+    (2592, 1024, 72, False, 11),
+    # the large kernel sooner where the activations are more than the caches hold, from K = 1280 on, and for its narrow tiles
+    (4400, 192, 2048, True, 4), (4400, 192, 1792, True, 11), (4064, 192, 2080, True, 11), (4352, 112, 2048, True, 4), (4080, 112, 2080, True, 11),
+    (4352, 112, 1920, True, 11), (1280, 1024, 512, True, 11), (1312, 1024, 512, True, 4), (1728, 1024, 320, True, 11), (1824, 1024, 320, True, 4)])
 def test_small_outputs_where_they_are_the_faster_kernel(nq, M, N, K, i8, family):
     case = make_case(nq, N, K, 8, 2, seed=M + K)
     x = inputs.uniform_activations((M, K), seed=K)
@@ -174,6 +180,23 @@ def test_small_outputs_or_stationary_rows(nq, B, H, Cin, k, N, int8, family):
     torch.cuda.synchronize()
     assert nq.nq_profile_last_kernel()[0] == family
     acc = oracle.conv_acc(x, case.ow_full.reshape(N, k, k, Cin), 1, pad)
+    check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, int8)
+
+
+@pytest.mark.parametrize("k,stride,pad,Cin,N,int8,family", [(2, 1, 0, 32, 96, False, 11), (1, 1, 1, 128, 96, False, 11), (1, 2, 1, 128, 72, False, 11),
+                                                            (1, 1, 0, 128, 96, False, 9), (1, 1, 0, 128, 96, True, 11)])
+def test_small_outputs_at_128_long_reductions(nq, k, stride, pad, Cin, N, int8, family):
+    # the stationary kernel's limit for one block of columns is for what it can take: neither filters nor padding
+    H = 32 if stride == 1 else 66
+    x = inputs.uniform_activations((8, H, H, Cin), seed=N)
+    case = make_case(nq, N, k * k * Cin, 8, 2, seed=N + k)
+    lead = (8,) + oracle.conv_out_hw(H, H, k, k, stride, pad)
+    epi, _, okw = epi_pair(nq, case, True, lead, dump=False, s_a=0.02, out_int8=int8, inv_s_out=4.0)
+    y = torch.full(lead + (N,), 77, dtype=torch.int8 if int8 else torch.float32, device="cuda")
+    nq.nq_conv_full(dev(x), nq.nq_conv_shape(8, H, H, Cin, N, k, k, stride, pad), case.W.desc, epi, y)
+    torch.cuda.synchronize()
+    assert nq.nq_profile_last_kernel()[0] == family
+    acc = oracle.conv_acc(x, case.ow_full.reshape(N, k, k, Cin), stride, pad)
     check_outputs(host(y), None, oracle.epilogue(acc, **okw), acc, int8)
 
 
