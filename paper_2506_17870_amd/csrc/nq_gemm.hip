@@ -563,8 +563,8 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
     //   of more than 8 MB, which the column tiles read again from memory: 770 1.3 (0.94), 950 0.74 to 1.1;
     //   large, longer K, up to 128 columns (its narrow tiles): 512 blocks 1.65 (1.1), 640 1.3 (1.0); 560 with more than 8 MB 0.9;
     //   K below 640 900 1.6, 1000 1.3 (0.92);
-    //   generic, filters over multiples of 32 channels: 2860 blocks 1.4, 3460 1.3 (1.0); over other multiples of 8: K below 64 3000
-    //   1.2, 4400 0.8; K below 256 4600 1.5 (steps of 16: 4000 1.2 (1.02), 4600 1.0 (0.88)); K below 1024 3400 1.2 (1.02); longer 1500 1.9
+    //   generic, filters over multiples of 32 channels: 2860 blocks 1.4, 3460 1.3 (1.0); over other multiples of 8: K up to 64 3000
+    //   1.1 to 1.2, 3900 0.9, 4400 0.8; K below 256 4600 1.5 (steps of 16: 4000 1.2 (1.02), 4600 1.0 (0.88)); K below 1024 3400 1.2 (1.02); longer 1500 1.9
     //   (1.28), 2000 1.35 (0.83), and from K = 6144 on 1170 2.2, 1520 0.93;
     //   generic, filters over other multiples of 4, which it gathers byte by byte: 1.4 to 72, at any number up to 49000;
     //   few channels (4 or 8): 660 blocks 5.4, 2900 2.8, 6900 1.5 to 2.1.
@@ -605,7 +605,7 @@ nq_status run(bool full, const int8_t *d_x, const Geometry &g, const nq_weight *
         if (windowed) slab_most = 2048;
         else if (few_channels) slab_most = 6500;
         else if (g.Cin % 8 == 4) slab_most = INT64_MAX;
-        else if (g.Cin % 32 != 0) slab_most = w->K < 64 ? 3072 : w->K < 256 ? (g.Cin % 16 == 0 ? 4096 : 4600) : w->K < 1024 ? 3400 : w->K < 6144 ? 1800 : 1280;
+        else if (g.Cin % 32 != 0) slab_most = w->K <= 64 ? 3072 : w->K < 256 ? (g.Cin % 16 == 0 ? 4096 : 4600) : w->K < 1024 ? 3400 : w->K < 6144 ? 1800 : 1280;
         else slab_most = 3072;
     } else if (stat_shape) {
         slab_most = ragged ? 1280 : 2048;              // at any stride
