@@ -27,6 +27,6 @@ def __getattr__(name):
 def _forget(*names):
     """Called by the binding when attributes of its own are replaced: the next access through the package asks it again."""
     for name in names or list(_copied):
-        value = _copied.pop(name, None)
-        if value is not None and globals().get(name) is value:       # (the caller may have put something else here)
-            del globals()[name]
+        value = _copied.pop(name, _copied)
+        if value is not _copied and globals().get(name, _copied) is value:       # (the caller may have put something else here)
+            globals().pop(name, None)

@@ -112,6 +112,10 @@ def test_replaced_functions_are_seen_through_the_package(nq, monkeypatch):
     del nq.binding.extra
     with pytest.raises(AttributeError):
         nq.extra
+    monkeypatch.setattr(nq.binding, "extra", None, raising=False)
+    assert nq.extra is None
+    monkeypatch.setattr(nq.binding, "extra", 2)
+    assert nq.extra == 2
 
 
 @pytest.mark.parametrize("full", [True, False])
