@@ -354,7 +354,7 @@ def nq_gconv_part(d_x, shape: nq_conv_shape, groups: int, w: nq_weight, epi: nq_
                               _stream(stream)), "nq_gconv_part")
 
 
-_LAYER_CALLS = (nq_conv_full, nq_conv_part, nq_gemm_full, nq_gemm_part)
+_GEMM_CALLS, _CONV_CALLS = (nq_gemm_part, nq_gemm_full), (nq_conv_part, nq_conv_full)
 
 
 def run_layer(full, d_x, sizes, w: nq_weight, act_scale, d_bias, d_residual, residual_scale, relu, out_int8, inv_out_scale, d_y,
@@ -364,7 +364,8 @@ def run_layer(full, d_x, sizes, w: nq_weight, act_scale, d_bias, d_residual, res
     longer to make than its launch)."""
     gemm = isinstance(sizes, int)
     call = (nq_gemm_full if full else nq_gemm_part) if gemm else (nq_conv_full if full else nq_conv_part)
-    if call in _LAYER_CALLS:             # else somebody times or records the calls: their function gets this one, too
+    # (otherwise somebody times or records the calls: their function gets this one, too)
+    if call is (_GEMM_CALLS if gemm else _CONV_CALLS)[1 if full else 0]:
         st = _fast.layer(full, d_x, sizes if gemm else 0, None if gemm else sizes, w, act_scale, d_bias, d_residual, residual_scale, relu,
                          out_int8, inv_out_scale, d_y, stream if stream is None else _stream(stream))
         if st >= 0:

@@ -133,6 +133,19 @@ def test_the_walkers_layers_reach_replaced_functions(nq, monkeypatch, kind, full
     assert (x, y, stream, e.act_scale, e.relu, e.out_int8, e.inv_out_scale) == (A, A, 0, 0.5, 1, 1, 2.0)
 
 
+def test_the_walkers_layers_reach_one_call_in_anothers_place(nq, monkeypatch):
+    w = weight(nq, resident=False)
+    args = (A, 1, w, 0.5, None, None, 0.0, True, True, 2.0, A, 0)
+    with pytest.raises(nq.NQError) as err:
+        nq.run_layer(True, *args)
+    assert err.value.status == nq.NQ_ERR_NOT_RESIDENT
+    seen = []
+    monkeypatch.setattr(nq.binding, "run_layer_by_calls", lambda *a: seen.append(a))
+    monkeypatch.setattr(nq.binding, "nq_gemm_full", nq.binding.nq_gemm_part)
+    nq.run_layer(True, *args)
+    assert len(seen) == 1
+
+
 def test_an_extension_that_is_not_there_is_named(nq):
     import subprocess
     import sys
