@@ -412,7 +412,21 @@ def test_filters_of_channels_in_small_steps(nq, B, H, W, Cin, N, k, stride, pad,
     (35, 56, 56, 32, 3, 1), (18, 56, 120, 32, 3, 11), (19, 56, 120, 32, 3, 1), (32, 14, 272, 160, 3, 11), (33, 14, 272, 192, 3, 4),
     (66, 56, 8, 32, 3, 11), (67, 56, 8, 32, 3, 5), (3, 56, 2, 32, 3, 5), (31, 56, 32, 32, 3, 11), (32, 56, 32, 32, 3, 1)])
 def test_filters_in_small_steps_or_the_kernel_they_replace(nq, B, H, Cin, N, k, family):
-    # routes, and values on grids this large: every image against the generic kernel's, the first and the last against the oracle's
+    # routes alone, on images of zeros: outputs of each kernel are compared elsewhere
+    case = make_case(nq, N, k * k * Cin, 8, 2, seed=Cin + N)
+    cs = nq.nq_conv_shape(B, H, H, Cin, N, k, k, 1, k // 2)
+    bias = inputs.small_floats(N, 0.2, seed=N)
+    epi, _, _ = epi_pair(nq, case, True, (B, H, H), dump=False, s_a=0.02, bias=bias)
+    y = torch.full((B, H, H, N), 77, dtype=torch.float32, device="cuda")
+    nq.nq_conv_full(torch.zeros(B, H, H, Cin, dtype=torch.int8, device="cuda"), cs, case.W.desc, epi, y)
+    torch.cuda.synchronize()
+    assert nq.nq_profile_last_kernel()[0] == family
+    assert torch.equal(y, torch.from_numpy(bias).to(y).expand_as(y))
+
+
+@pytest.mark.parametrize(*test_filters_in_small_steps_or_the_kernel_they_replace.pytestmark[0].args)
+def test_values_of_filters_in_small_steps_on_large_grids(nq, B, H, Cin, N, k, family):
+    # values on the grids above: every image against the generic kernel's, the first and the last against the oracle's
     case = make_case(nq, N, k * k * Cin, 8, 2, seed=Cin + N)
     cs = nq.nq_conv_shape(B, H, H, Cin, N, k, k, 1, k // 2)
     bias = inputs.small_floats(N, 0.2, seed=N)
